@@ -720,18 +720,30 @@ LaunchPlan plan_launch(c2f_ctx* ctx, int64_t cells, int32_t total_items, int32_t
             lp.block = it->second.block;
             lp.cap = it->second.list_cap;
         } else {
-            // At most one replication per compute unit on a large grid:
-            // wide groups, since nothing else would use the unit.  FP64
-            // keeps 512 threads (2 waves per SIMD, 256 VGPRs); at 1024 it
-            // would be held to 128 VGPRs and spill (8192^2 x 64 reps: 10.1
-            // ms at 512, 12.8 at 256, 18.8 at 1024).  FP32 single fires take
-            // 768 threads: 3 waves per SIMD fit the FP32 kernel's 168
-            // VGPRs with a 20-byte spill (2048^2 single fire: 3.97 ms at
-            // 768, 4.02 at 1024, 4.25 at 512).
-            if (cells >= (1 << 20) && total_items <= ctx->n_cu)
-                lp.block = (precision == 1 && total_items <= 16) ? 768 : 512;
-            else
+            // Wide groups (1024 threads, one per compute unit) while a
+            // replication has a compute unit, or nearly one, to itself.  More
+            // replications than that are better served by two groups of 512
+            // threads a unit, and many small grids, whose periods hold few
+            // cells, by four of 256.  Kernel times in ms at 1024 / 512 / 256
+            // threads, FP64 results, 48 periods (64^2: 24):
+            //   1024^2   256 replications   4.88 /  5.67 /  8.46
+            //   1024^2   768                7.44 /  6.45 /  9.14
+            //    512^2   512                5.32 /  5.58 /  7.46
+            //    512^2  2048               14.9  / 10.5  / 10.6
+            //    256^2   512                4.13 /  3.78 /  5.22
+            //    256^2  2048               11.5  /  7.90 /  7.21
+            //     64^2   512                1.22 /  0.90 /  0.96
+            //     64^2  2048                3.68 /  2.22 /  1.51
+            // FP64 results on large grids keep 512-thread groups.
+            const int64_t n_cu = ctx->n_cu, items = total_items;
+            if (precision == 0 && items <= n_cu && cells >= (1 << 20))
+                lp.block = 512;
+            else if (items <= n_cu || (items <= 2 * n_cu && cells >= (1 << 18)))
+                lp.block = 1024;
+            else if (items > 4 * n_cu && cells <= (1 << 16))
                 lp.block = 256;
+            else
+                lp.block = 512;
             lp.cap = default_list_cap(cells, total_items);
         }
         if (ctx->block_override) lp.block = ctx->block_override;

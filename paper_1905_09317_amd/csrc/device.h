@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fuel_table.h"
 #include "ln64.h"
 #include "types.h"
@@ -235,9 +237,19 @@ __device__ __forceinline__ double isf_curve(const CoefR<double>& k, double sfc, 
     return -ln_f64(t) * recip(k.b);
 }
 
-__device__ __forceinline__ double slope_wind(const CoefR<double>* coef, int f, double sfc, double sfd,
-                                          const double* row, const LandR<double>& L) {
+// WSE of a slope-adjusted spread index.
+__device__ __forceinline__ double wse_of_isf(double isf, const double* row) {
     const double ff = row[0], isz = row[1];
+    double wse = ln_f64(isf * recip(isz)) * (1.0 / 0.05039);
+    if (wse > 40.0) {
+        wse = (isf < 0.999 * 2.496 * ff) ? 28.0 - ln_f64(1.0 - isf * recip(2.496 * ff)) * (1.0 / 0.0818) : 112.45;
+    }
+    return wse;
+}
+
+template <typename LAND>
+__device__ __forceinline__ double slope_wind(const CoefR<double>* coef, int f, double sfc, double sfd,
+                                          const double* row, const LAND& L) {
     // every lane inverts its own (or the C-2) curve; the D-1 curve only runs
     // when some lane of the wave is mixedwood
     const bool mix_pc = is_mix_pc(f), mixed = mix_pc || is_mix_pdf(f);
@@ -250,11 +262,7 @@ __device__ __forceinline__ double slope_wind(const CoefR<double>* coef, int f, d
             isf = w * isf + (1.0 - w) * d1;
         }
     }
-    double wse = ln_f64(isf * recip(isz)) * (1.0 / 0.05039);
-    if (wse > 40.0) {
-        wse = (isf < 0.999 * 2.496 * ff) ? 28.0 - ln_f64(1.0 - isf * recip(2.496 * ff)) * (1.0 / 0.0818) : 112.45;
-    }
-    return wse;
+    return wse_of_isf(isf, row);
 }
 
 // The same in FP32 for the ordinary branch (WSE <= 40 km/h).  ln(1 - x) is
@@ -314,6 +322,22 @@ __device__ __forceinline__ R c6_rate(R rss, R isi, R rso, R fme_r) {
     return rss + cfb * ((R)60 * -m_expm1((R)-0.0497 * isi) * fme_r - rss);
 }
 
+// Unit vector pointing upslope (east, north) from the Horn numerators.
+template <typename R>
+__device__ __forceinline__ void upslope_unit(int gx, int gn, R& ux, R& uy) {
+    const R ig = recip(m_sqrt((R)gx * (R)gx + (R)gn * (R)gn));
+    ux = (R)gx * ig;
+    uy = (R)gn * ig;
+}
+// The same of a cell's record, which holds the FP32 one.
+__device__ __forceinline__ void upslope(const CellRec& rec, float& ux, float& uy) {
+    ux = rec.ux;
+    uy = rec.uy;
+}
+__device__ __forceinline__ void upslope(const CellRec& rec, double& ux, double& uy) {
+    upslope_unit<double>(rec_gx(rec.grad), rec_gn(rec.grad), ux, uy);
+}
+
 // Everything is evaluated in R.  In FP32 the slope-equivalent wind switches
 // to FP64 from 39 km/h up: inverting the rate curve near its asymptote (the
 // WSE > 40 branch) turns a relative error of 1e-7 in ISF into ~1e-4 in WSE.
@@ -335,9 +359,10 @@ __device__ __forceinline__ CellRates<R> cell_rates(const CoefR<R>* coef, const C
             need64 = ill || !(wse < 39.0f);
         }
         if (need64) wse = (R)slope_wind(coef64, f, rec.sfc, rec.sfd, row64, L64);
-        const R ig = recip(m_sqrt((R)gx * (R)gx + (R)gn * (R)gn));
-        wx += wse * ((R)gx * ig);                                          // along the upslope unit vector
-        wy += wse * ((R)gn * ig);
+        R ux, uy;
+        upslope(rec, ux, uy);
+        wx += wse * ux;
+        wy += wse * uy;
     }
     const R wsv = m_sqrt(wx * wx + wy * wy);
     // exp(0.05039 WSV) is f(W) up to 40 km/h, and its reciprocal is the back
@@ -487,8 +512,8 @@ static __constant__ CrownCoef kCrown[kNumFuels] = {C2F_CROWN_ROWS};
 // burned CFB = 1 - exp(-0.23 (S - RSO)) above the critical surface rate RSO
 // = CSI / (300 SFC) (S the head rate, the surface rate for C-6; 0 for fuels
 // that do not crown).  *cfb (may be NULL) receives CFB.
-template <typename R>
-__device__ __forceinline__ R head_intensity(const CellRates<R>& cr, int f, const R* row, const LandR<R>& L,
+template <typename R, typename LAND>
+__device__ __forceinline__ R head_intensity(const CellRates<R>& cr, int f, const R* row, const LAND& L,
                                             R* cfb_out) {
     R sfc = row[kRowSFC + f];
     if (is_mix_pc(f)) sfc = L.pc_w * row[kRowSFC + kC2] + ((R)1 - L.pc_w) * row[kRowSFC + kD1];
@@ -605,7 +630,7 @@ __device__ __forceinline__ bool axis_q_direct(const RateCtx<R>& X, const CellRec
     }
     axis_rates_q<R>(cr, mu, X.rounding != 0, ua, ub, q);
     if (X.hfi_min > 0.f) {
-        const R hfi = head_intensity<R>(cr, rec_fuel(rec.info), X.rows + ro, X.L, nullptr) * mu;
+        const R hfi = head_intensity(cr, rec_fuel(rec.info), X.rows + ro, X.L, (R*)nullptr) * mu;
         return !((double)hfi >= (double)X.hfi_min);
     }
     return false;
@@ -659,7 +684,7 @@ __device__ __forceinline__ bool axis_q(const RateCtx<R>& X, const CellRec& rec, 
             bool faint = false;
             if (X.hfi_min > 0.f) {
                 const double hfi =
-                    (double)(head_intensity<float>(cr, rec_fuel(rec.info), X.rows32 + ro, X.L32, nullptr) * mu);
+                    (double)(head_intensity(cr, rec_fuel(rec.info), X.rows32 + ro, X.L32, (float*)nullptr) * mu);
                 const double hm = (double)X.hfi_min;
                 exact = exact && fabs(hfi - hm) > kMixMarginH * hm;
                 faint = !(hfi >= hm);
@@ -676,6 +701,562 @@ __device__ __forceinline__ R head_rate(const RateCtx<R>& X, const CellRec& rec, 
     const size_t ro = (size_t)period * X.row_stride;
     const CellRates<R> cr = cell_rates<R>(X.coef, X.coef64, rec, X.rows + ro, X.rows64 + ro, X.L, X.L64);
     return cr.h * noise_mult<R>(X.seed, cell, period, X.rep, X.sigma);
+}
+
+// ---------------------------------------------------------- four lanes a cell
+// The propagation kernel gives a cell to a quad: four neighbouring lanes,
+// lane k of which takes the opposite axes k and k + 4.  What the axes share
+// is split by role instead of being repeated: the rate curves a (1 -
+// exp(-b x))^c of the head and the back fire and the length-to-breadth curve
+// of the same form run side by side in lanes 0, 1 and 2, the two slope
+// inversions of a mixedwood in lanes 0 and 1, and the random blocks of tags
+// 0, 1 and 2 in lanes 0, 1 and 2.  Every value is formed by the operations of
+// cell_rates, noise_mult and axis_rates, in their order, so the results are
+// the same bits.  All four lanes of a quad are active together and agree on
+// every branch.
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// x of lane K of the quad.
+template <int K>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t x) { return quad_perm<K * 0x55>(x); }
+template <int K>
+__device__ __forceinline__ float quad_lane(float x) { return __uint_as_float(quad_lane<K>(__float_as_uint(x))); }
+template <int K>
+__device__ __forceinline__ double quad_lane(double x) {
+    return __hiloint2double((int)quad_lane<K>((uint32_t)__double2hiint(x)),
+                            (int)quad_lane<K>((uint32_t)__double2loint(x)));
+}
+// Bitwise or over the quad, in every lane.
+__device__ __forceinline__ uint32_t quad_or(uint32_t x) {
+    x |= quad_perm<0xB1>(x);          // lane ^ 1
+    return x | quad_perm<0x4E>(x);    // lane ^ 2
+}
+
+// Entries of a quad's coefficient tables: the fuels, then the length-to-
+// breadth curves 8.729 (1 - exp(-0.030 WSV))^2.155 and (grass, on the wind
+// speed itself) 1.1 WSV^0.464.
+constexpr int kCurveLB = kNumFuels;
+constexpr int kNumCurves = kNumFuels + 2;
+
+template <typename R>
+__device__ __forceinline__ CoefR<R> curve_entry(int i) {
+    if (i < kNumFuels) return coef_table<R>()[i];
+    return i == kCurveLB ? CoefR<R>{(R)8.729, (R)0.030, (R)2.155, (R)0, (R)0}
+                         : CoefR<R>{(R)1.1, (R)0, (R)0.464, (R)0, (R)0};
+}
+
+// Landscape constants in LDS (LandR's fields, with the intensities beside them).
+template <typename R>
+struct LandLds {
+    R pc_w, cf, pdf_w, fme_r;
+    R csi[kNumFuels];
+};
+template <typename R> __device__ __forceinline__ void load_land(const LandDev* D, LandLds<R>& L, int f);
+template <> __device__ __forceinline__ void load_land<double>(const LandDev* D, LandLds<double>& L, int f) {
+    L.csi[f] = D->csi64[f];
+    if (f == 0) {
+        L.pc_w = D->pc_w64;
+        L.cf = D->cf64;
+        L.pdf_w = D->pdf_w64;
+        L.fme_r = D->fme_r64;
+    }
+}
+template <> __device__ __forceinline__ void load_land<float>(const LandDev* D, LandLds<float>& L, int f) {
+    L.csi[f] = D->csi32[f];
+    if (f == 0) {
+        L.pc_w = D->pc_w32;
+        L.cf = D->cf32;
+        L.pdf_w = D->pdf_w32;
+        L.fme_r = D->fme_r32;
+    }
+}
+
+// What the evaluations of one replication and period read from LDS: the
+// curves, the period's weather rows and the landscape's constants in one
+// precision.
+template <typename R>
+struct EvalLds {
+    CoefR<R> coef[kNumCurves];
+    R row[kRowLen];
+    LandLds<R> L;
+};
+// The rest, uniform over the work group.
+struct EvalRep {
+    uint64_t seed;
+    uint32_t rep;
+    int32_t rounding;
+    float sigma, hfi_min;
+};
+
+// The functions an evaluation uses: those of cell_rates and noise_mult, or
+// (FP32 only) the hardware's base-2 logarithm and exponential, square root and
+// cosine of a fraction of a turn.
+template <typename R>
+struct MathOf {
+    static __device__ __forceinline__ R exp_wind(R x) { return m_exp(x); }
+    static __device__ __forceinline__ R exp_noise(R x) { return m_exp(x); }
+    static __device__ __forceinline__ R one_minus_exp(R y) { return -m_expm1(-y); }   // 1 - exp(-y)
+    static __device__ __forceinline__ R log(R x) { return m_log(x); }
+    static __device__ __forceinline__ R sqrt(R x) { return m_sqrt(x); }
+    static __device__ __forceinline__ R cos_turn(R u) { return cos_2pi(u); }
+    static __device__ __forceinline__ R pow(R x, R y) { return rate_pow(x, y); }
+    static __device__ __forceinline__ R log1m(R x) { return log_1m(x); }
+};
+// Largest errors over grids of 2^24 arguments, and those of the library's
+// FP32 functions: ln of the noise draw's u1, as the radius sqrt(-2 ln u1),
+// 4.9e-7 absolute (5.3e-7); the cosine 1.3e-7 absolute (0.5e-7); ln over
+// [1, 11] 1.6e-7 relative (1.6e-7); ln(1 - x) over (0, 0.99] 2.8e-7 relative
+// (2.7e-7); the square root 0.9e-7 relative; exp_wind over winds of 0 to 150
+// km/h 1.4e-7 relative (0.8e-7; 5.0e-7 without the correction of the
+// product's rounding).
+struct MathFast {
+    static constexpr float kLog2e = 1.44269504088896340736f, kLog2eLow = 1.925963033e-8f;
+    static constexpr float kLn2 = 0.69314718055994530942f;
+    static __device__ __forceinline__ float exp_wind(float x) {
+        const float p = x * kLog2e;
+        const float d = fmaf(x, kLog2eLow, fmaf(x, kLog2e, -p));   // what p lost
+        const float y = __builtin_amdgcn_exp2f(p);
+        return fmaf(y * d, kLn2, y);
+    }
+    static __device__ __forceinline__ float exp_noise(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
+    // 1 - exp(-y), y >= 0: with u = exp(-y) rounded, 1 - u where u < 1/2, and
+    // above it (1 - u) y / -ln(u), which corrects the rounding of u
+    static __device__ __forceinline__ float one_minus_exp(float y) {
+        const float p = y * -kLog2e;
+        const float u = __builtin_amdgcn_exp2f(p);
+        const float d = 1.0f - u;
+        const float r = d * (p * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(u)));
+        return u < 0.5f ? d : (u == 1.0f ? y : r);
+    }
+    static __device__ __forceinline__ float log(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
+    static __device__ __forceinline__ float sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+    static __device__ __forceinline__ float cos_turn(float u) { return __builtin_amdgcn_cosf(u); }
+    static __device__ __forceinline__ float pow(float x, float y) {
+        return __builtin_amdgcn_exp2f(y * __builtin_amdgcn_logf(x));
+    }
+    static __device__ __forceinline__ float log1m(float x) {
+        const float u = 1.0f - x;
+        const float r = log(u) * (x * __builtin_amdgcn_rcpf(1.0f - u));
+        return u == 1.0f ? -x : r;
+    }
+};
+
+// FP64 slope wind of an FP32 evaluation near the inversion's asymptote.
+// Rare, and kept out of line: inlined, its constants and temporaries take
+// registers from the FP32 evaluation around it.
+static inline __device__ __attribute__((noinline)) float slope_wind_rare(const EvalLds<double>* x, int f, double sfc,
+                                                                  double sfd) {
+    return (float)slope_wind(x->coef, f, sfc, sfd, x->row, x->L);
+}
+
+template <typename R, typename M>
+__device__ __forceinline__ R quad_slope_wind(const EvalLds<R>& x, const EvalLds<double>& x64, const CellRec& rec,
+                                             int f, int role) {
+    const bool mix_pc = is_mix_pc(f), mixed = mix_pc || is_mix_pdf(f);
+    const int fs = role == 1 ? (int)kD1 : mix_pc ? (int)kC2 : f;
+    const R g = x.row[kRowG + fs], b = x.coef[fs].b;
+    if constexpr (sizeof(R) == 4) {
+        const float t = (role == 1 ? (float)rec.sfd : (float)rec.sfc) * g;
+        const float l = -M::log1m(t > 0.99f ? 0.99f : t) * recip(b);
+        const uint32_t over = t > kIllX ? 1u : 0u;
+        const float own = quad_lane<0>(l), d1 = quad_lane<1>(l);
+        const uint32_t o0 = quad_lane<0>(over), o1 = quad_lane<1>(over);
+        float isf = own;
+        if (mixed) {
+            const float w = mix_pc ? x.L.pc_w : x.L.pdf_w;
+            isf = w * own + (1.0f - w) * d1;
+        }
+        const float wse = M::log(isf * recip(x.row[1])) * (1.0f / 0.05039f);
+        if (o0 != 0u || (mixed && o1 != 0u) || !(wse < 39.0f)) return slope_wind_rare(&x64, f, rec.sfc, rec.sfd);
+        return wse;
+    } else {
+        double t = 1.0 - (role == 1 ? rec.sfd : rec.sfc) * g;
+        if (t < 0.01) t = 0.01;
+        const double l = -ln_f64(t) * recip(b);
+        const double own = quad_lane<0>(l), d1 = quad_lane<1>(l);
+        double isf = own;
+        if (mixed) {
+            const double w = mix_pc ? x.L.pc_w : x.L.pdf_w;
+            isf = w * own + (1.0 - w) * d1;
+        }
+        return wse_of_isf(isf, x.row);
+    }
+}
+
+// cell_rates of a quad's cell; `role` is the lane's number in the quad.
+template <typename R, typename M>
+__device__ __forceinline__ CellRates<R> quad_cell_rates(const EvalLds<R>& x, const EvalLds<double>& x64,
+                                                        const CellRec& rec, int role) {
+    const int f = rec_fuel(rec.info);
+    R wx = x.row[2], wy = x.row[3];
+    if (rec.grad != 0u) {
+        const R wse = quad_slope_wind<R, M>(x, x64, rec, f, role);
+        R ux, uy;
+        upslope(rec, ux, uy);
+        wx += wse * ux;
+        wy += wse * uy;
+    }
+    const R wsv = M::sqrt(wx * wx + wy * wy);
+    const R ew = M::exp_wind((R)0.05039 * wsv);
+    R fw = ew;
+    if (!(wsv <= (R)40)) fw = (R)12 * M::one_minus_exp((R)0.0818 * (wsv - (R)28));
+    const R isz = x.row[1];
+    // lane 0: the head curve, lane 1: the back curve, lane 2: LB (lane 3
+    // repeats the head curve)
+    const bool grass = is_grass(f), mix_pc = is_mix_pc(f), mixed = mix_pc || is_mix_pdf(f);
+    const R rew = recip(ew);
+    const R isi = isz * (role == 1 ? rew : fw);
+    const CoefR<R>& k = x.coef[role == 2 ? kCurveLB + (int)grass : mix_pc ? (int)kC2 : f];
+    R base = M::one_minus_exp(k.b * (role == 2 ? wsv : isi));
+    base = (role == 2 && grass) ? wsv : base;
+    const R curve = k.a * M::pow(base, k.c);
+    R r = curve;
+    if (__any(mixed)) {
+        const R d1 = x.coef[kD1].a * M::pow(M::one_minus_exp(x.coef[kD1].b * isi), x.coef[kD1].c);
+        if (mixed) {
+            const R w = mix_pc ? x.L.pc_w : x.L.pdf_w;
+            const R wd1 = (f == kM2 || f == kM4) ? (R)0.2 * ((R)1 - w) : ((R)1 - w);
+            r = w * r + wd1 * d1;
+        }
+    }
+    if (grass) r = r * x.L.cf;
+    r = r * x.row[kRowBE + f];
+    CellRates<R> out;
+    out.rss = quad_lane<0>(r);
+    if (__any(f == kC6)) {
+        if (f == kC6) {
+            const R sfc = x.row[kRowSFC + kC6];
+            const R rso = sfc > (R)0 ? x.L.csi[kC6] * recip((R)300 * sfc) : (R)3.0e38;
+            r = c6_rate<R>(r, isi, rso, x.L.fme_r);
+        }
+    }
+    out.h = quad_lane<0>(r);
+    out.b = quad_lane<1>(r);
+    const R lb = quad_lane<2>(curve);
+    out.lbm1 = grass ? ((wsv >= (R)1) ? lb - (R)1 : (R)0) : lb;
+    out.lb = (R)1 + out.lbm1;
+    out.wx = wx;
+    out.wy = wy;
+    out.wsv = wsv;
+    // wsv - 40 and wsv - 1 are exact wherever they are small
+    out.edge = (R)fabs(wsv - (R)40) < (R)kEdgeWsv || (grass && (R)fabs(wsv - (R)1) < (R)kEdgeWsv);
+    return out;
+}
+
+// The random words of a quad's cell: u1, u2 of the noise draw (tag 0) and,
+// with stochastic rounding, the words of the lane's two axes (tags 1, 2).
+struct QuadWords {
+    uint32_t n1, n2, wa, wb;
+};
+__device__ __forceinline__ QuadWords quad_words(uint64_t seed, uint32_t cell, uint32_t period, uint32_t rep,
+                                                int role) {
+    // the key schedule is kept inside the pass: hoisted out of the loops its
+    // twenty words take scalar registers from everything else
+    uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    const uint4 x = philox4x32_10(make_uint4(cell, period, rep, (uint32_t)role), k0, k1);
+    QuadWords o;
+    o.n1 = quad_lane<0>(x.x);
+    o.n2 = quad_lane<0>(x.y);
+    // the exchanges come before the selection: a lane reads its neighbours
+    // while all four are active
+    const uint32_t a0 = quad_lane<1>(x.x), a1 = quad_lane<1>(x.y), a2 = quad_lane<1>(x.z), a3 = quad_lane<1>(x.w);
+    const uint32_t b0 = quad_lane<2>(x.x), b1 = quad_lane<2>(x.y), b2 = quad_lane<2>(x.z), b3 = quad_lane<2>(x.w);
+    const uint32_t a01 = (role & 1) ? a1 : a0, a23 = (role & 1) ? a3 : a2;
+    const uint32_t b01 = (role & 1) ? b1 : b0, b23 = (role & 1) ? b3 : b2;
+    o.wa = (role & 2) ? a23 : a01;
+    o.wb = (role & 2) ? b23 : b01;
+    return o;
+}
+
+// noise_mult from the draw's words.
+template <typename R, typename M>
+__device__ __forceinline__ R noise_of(uint32_t n1, uint32_t n2, R sigma) {
+    const R u1 = ((R)(n1 >> 8) + (R)1) * (R)(1.0 / 16777216.0);
+    const R u2 = unit24<R>(n2);
+    const R z = M::sqrt((R)-2 * M::log(u1)) * M::cos_turn(u2);
+    return M::exp_noise(sigma * z - (R)0.5 * sigma * sigma);
+}
+
+// The rates of axes `role` (xa) and `role` + 4 (xb).  The axes point opposite
+// ways, so at most one of them lies in the front half.
+template <typename R, typename M>
+__device__ __forceinline__ void quad_axis_rates(const CellRates<R>& cr, R mu, int role, R& xa, R& xb) {
+    const R a = (R)0.5 * (cr.h + cr.b);
+    const R il = recip(cr.lb);
+    const R il2 = il * il;
+    const R base = a * il2;
+    const R e = M::sqrt(cr.lbm1 * (cr.lbm1 + (R)2)) * il;
+    const R one_m_e = il2 * recip((R)1 + e);
+    const R inv_wsv = (cr.wsv > (R)0) ? recip(cr.wsv) : (R)0;
+    const R cx = cr.wx * inv_wsv, cy = cr.wy * inv_wsv;
+    const R s = (R)0.70710678118654752440;
+    const R ux = role == 0 ? (R)1 : role == 1 ? s : role == 2 ? (R)0 : -s;
+    const R uy = role == 0 ? (R)0 : role == 2 ? (R)1 : s;
+    const R c = ux * cx + uy * cy;
+    const bool fa = c > (R)0, fb = c < (R)0;
+    const R dx = cx - (fb ? -ux : ux), dy = cy - (fb ? -uy : uy);
+    const R front = base * recip(one_m_e + e * ((R)0.5 * (dx * dx + dy * dy)));
+    xa = mu * (fa ? front : base);
+    xb = mu * (fb ? front : base);
+}
+
+template <typename R>
+__device__ __forceinline__ int32_t quantise(R x, R u) {
+    const R v = m_floor(x + u);
+    return (v < (R)1073741824) ? (int32_t)v : 1073741824;
+}
+
+// axis_q_direct of a quad's cell: qa and qb are the integer rates of axes
+// `role` and `role` + 4.
+template <typename R>
+__device__ __forceinline__ bool quad_axis_q_direct(const EvalLds<R>& x, const EvalLds<double>& x64, const EvalRep& e,
+                                                   const CellRec& rec, const QuadWords& w, int role, int32_t& qa,
+                                                   int32_t& qb) {
+    const CellRates<R> cr = quad_cell_rates<R, MathOf<R>>(x, x64, rec, role);
+    const R mu = e.sigma == 0.f ? (R)1 : noise_of<R, MathOf<R>>(w.n1, w.n2, (R)e.sigma);
+    R xa, xb;
+    quad_axis_rates<R, MathOf<R>>(cr, mu, role, xa, xb);
+    qa = quantise<R>(xa, e.rounding != 0 ? unit24<R>(w.wa) : (R)0.5);
+    qb = quantise<R>(xb, e.rounding != 0 ? unit24<R>(w.wb) : (R)0.5);
+    if (e.hfi_min > 0.f) {
+        const R hfi = head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (R*)nullptr) * mu;
+        return !((double)hfi >= (double)e.hfi_min);
+    }
+    return false;
+}
+
+// The FP64 evaluation of a quad whose FP32 one lies near a rounding boundary:
+// about 0.1 % of evaluations, kept out of line as slope_wind_rare is.
+struct QuadRates {
+    int32_t qa, qb;
+    uint32_t faint;
+};
+static inline __device__ __attribute__((noinline)) QuadRates quad_axis_q_rare(const EvalLds<double>* x, const EvalRep* e,
+                                                                       uint32_t info, uint32_t grad, double sfc,
+                                                                       double sfd, QuadWords w, int role) {
+    CellRec rec;
+    rec.info = info;
+    rec.grad = grad;
+    rec.ux = rec.uy = 0.f;   // the FP64 evaluation forms its own
+    rec.sfc = sfc;
+    rec.sfd = sfd;
+    QuadRates o;
+    o.faint = quad_axis_q_direct<double>(*x, *x, *e, rec, w, role, o.qa, o.qb) ? 1u : 0u;
+    return o;
+}
+
+// floor(x + u) of an FP64 rate known in FP32, if x32 + u lies clear of an
+// integer by the margin (sets exact = false if not).  The sum is formed in
+// FP32: its rounding, below 6.0e-8 (x + 1), and that of the distance from the
+// integer's middle widen kMixMargin by less than 2e-7 max(1, x).  Rates from
+// 16500 m/min up never pass.
+__device__ __forceinline__ int32_t quantise_mixed(float x, float u, bool& exact) {
+    const float v = x + u;
+    const float k = floorf(v);
+    const float clear = fmaf(-((float)kMixMargin + 2e-7f), fmaxf(1.0f, x), 0.5f);
+    exact = exact && fabsf((v - k) - 0.5f) < clear;
+    return (int32_t)k;
+}
+
+// axis_q of a quad's cell: FP32 rates (MIXED false), or the integer rates of
+// an FP64 evaluation.
+template <bool MIXED>
+__device__ __forceinline__ bool quad_axis_q(const EvalLds<float>& x, const EvalLds<double>& x64, const EvalRep& e,
+                                            const EvalRep* e_lds, const CellRec& rec, uint32_t cell, uint32_t period,
+                                            int role, int32_t& qa, int32_t& qb) {
+    QuadWords w{0u, 0u, 0u, 0u};
+    if (e.sigma != 0.f || e.rounding != 0) w = quad_words(e.seed, cell, period, e.rep, role);
+    if constexpr (!MIXED) {
+        return quad_axis_q_direct<float>(x, x64, e, rec, w, role, qa, qb);
+    } else {
+        const CellRates<float> cr = quad_cell_rates<float, MathFast>(x, x64, rec, role);
+        const float mu = e.sigma == 0.f ? 1.f : noise_of<float, MathFast>(w.n1, w.n2, e.sigma);
+        float xa, xb;
+        quad_axis_rates<float, MathFast>(cr, mu, role, xa, xb);
+        bool exact = !cr.edge;
+        qa = quantise_mixed(xa, e.rounding != 0 ? unit24<float>(w.wa) : 0.5f, exact);
+        qb = quantise_mixed(xb, e.rounding != 0 ? unit24<float>(w.wb) : 0.5f, exact);
+        bool faint = false;
+        if (e.hfi_min > 0.f) {
+            const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr) * mu);
+            const double hm = (double)e.hfi_min;
+            exact = exact && fabs(hfi - hm) > kMixMarginH * hm;
+            faint = !(hfi >= hm);
+        }
+        // a NaN rate fails the comparison above and goes the FP64 way
+        if (quad_or(exact ? 0u : 1u) == 0u) return faint;
+        const QuadRates o = quad_axis_q_rare(&x64, e_lds, rec.info, rec.grad, rec.sfc, rec.sfd, w, role);
+        qa = o.qa;
+        qb = o.qb;
+        return o.faint != 0u;
+    }
+}
+
+// ------------------------------------------------------------ one lane a cell
+// The same evaluation with a lane to each cell, for passes wide enough to
+// fill 64 of them: the axes' shared part is then formed once a cell instead
+// of four times.  The operations and their order are those of the quad, so
+// the rates are the same bits.  A cell that needs FP64 anywhere (its slope
+// wind, or its integer rates near a boundary) is only reported: a quad takes
+// it instead, so that no call and none of the FP64 constants are here.
+template <typename M>
+__device__ __forceinline__ float curve32(const CoefR<float>& k, float y) {
+    return k.a * M::pow(M::one_minus_exp(k.b * y), k.c);
+}
+
+template <typename M>
+__device__ __forceinline__ CellRates<float> lane_cell_rates(const EvalLds<float>& x, const CellRec& rec, bool& plain) {
+    const int f = rec_fuel(rec.info);
+    const bool grass = is_grass(f), mix_pc = is_mix_pc(f), mixed = mix_pc || is_mix_pdf(f);
+    const int fa = mix_pc ? (int)kC2 : f;
+    const bool any_mixed = __any(mixed);
+    plain = true;
+    float wx = x.row[2], wy = x.row[3];
+    if (rec.grad != 0u) {
+        const float t = (float)rec.sfc * x.row[kRowG + fa];
+        float isf = -M::log1m(t > 0.99f ? 0.99f : t) * recip(x.coef[fa].b);
+        bool ill = t > kIllX;
+        if (any_mixed) {
+            if (mixed) {
+                const float td = (float)rec.sfd * x.row[kRowG + kD1];
+                const float d1 = -M::log1m(td > 0.99f ? 0.99f : td) * recip(x.coef[kD1].b);
+                const float w = mix_pc ? x.L.pc_w : x.L.pdf_w;
+                isf = w * isf + (1.0f - w) * d1;
+                ill = ill || td > kIllX;
+            }
+        }
+        const float wse = M::log(isf * recip(x.row[1])) * (1.0f / 0.05039f);
+        plain = !ill && wse < 39.0f;
+        wx += wse * rec.ux;
+        wy += wse * rec.uy;
+    }
+    const float wsv = M::sqrt(wx * wx + wy * wy);
+    const float ew = M::exp_wind(0.05039f * wsv);
+    float fw = ew;
+    if (!(wsv <= 40.0f)) fw = 12.0f * M::one_minus_exp(0.0818f * (wsv - 28.0f));
+    const float isz = x.row[1], be = x.row[kRowBE + f];
+    const float isi_h = isz * fw, isi_b = isz * recip(ew);
+    float h = curve32<M>(x.coef[fa], isi_h), b = curve32<M>(x.coef[fa], isi_b);
+    if (any_mixed) {
+        if (mixed) {
+            const float w = mix_pc ? x.L.pc_w : x.L.pdf_w;
+            const float wd1 = (f == kM2 || f == kM4) ? 0.2f * (1.0f - w) : (1.0f - w);
+            h = w * h + wd1 * curve32<M>(x.coef[kD1], isi_h);
+            b = w * b + wd1 * curve32<M>(x.coef[kD1], isi_b);
+        }
+    }
+    if (grass) {
+        h = h * x.L.cf;
+        b = b * x.L.cf;
+    }
+    h = h * be;
+    b = b * be;
+    CellRates<float> out;
+    out.rss = h;
+    if (f == kC6) {
+        const float sfc = x.row[kRowSFC + kC6];
+        const float rso = sfc > 0.f ? x.L.csi[kC6] * recip(300.0f * sfc) : 3.0e38f;
+        h = c6_rate<float>(h, isi_h, rso, x.L.fme_r);
+        b = c6_rate<float>(b, isi_b, rso, x.L.fme_r);
+    }
+    out.h = h;
+    out.b = b;
+    const CoefR<float>& k = x.coef[kCurveLB + (int)grass];
+    float base = M::one_minus_exp(k.b * wsv);
+    base = grass ? wsv : base;
+    const float lb = k.a * M::pow(base, k.c);
+    out.lbm1 = grass ? (wsv >= 1.0f ? lb - 1.0f : 0.0f) : lb;
+    out.lb = 1.0f + out.lbm1;
+    out.wx = wx;
+    out.wy = wy;
+    out.wsv = wsv;
+    out.edge = fabsf(wsv - 40.0f) < kEdgeWsv || (grass && fabsf(wsv - 1.0f) < kEdgeWsv);
+    return out;
+}
+
+// The rates of all eight axes, pair by pair (axes k and k + 4 point opposite
+// ways, so at most one of them lies in the front half).
+template <typename M>
+__device__ __forceinline__ void lane_axis_rates(const CellRates<float>& cr, float mu, float* x8) {
+    const float a = 0.5f * (cr.h + cr.b);
+    const float il = recip(cr.lb);
+    const float il2 = il * il;
+    const float base = a * il2;
+    const float e = M::sqrt(cr.lbm1 * (cr.lbm1 + 2.0f)) * il;
+    const float one_m_e = il2 * recip(1.0f + e);
+    const float inv_wsv = (cr.wsv > 0.0f) ? recip(cr.wsv) : 0.0f;
+    const float cx = cr.wx * inv_wsv, cy = cr.wy * inv_wsv;
+    const float s = 0.70710678118654752440f;
+    const float ux[4] = {1.0f, s, 0.0f, -s}, uy[4] = {0.0f, s, 1.0f, s};
+    const float back = mu * base;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const float c = ux[k] * cx + uy[k] * cy;
+        const bool fb = c < 0.0f;
+        const float dx = cx - (fb ? -ux[k] : ux[k]), dy = cy - (fb ? -uy[k] : uy[k]);
+        const float front = mu * (base * recip(one_m_e + e * (0.5f * (dx * dx + dy * dy))));
+        x8[k] = c > 0.0f ? front : back;
+        x8[k + 4] = fb ? front : back;
+    }
+}
+
+// axis_q of one cell a lane, called by the whole wave together.  done = false:
+// the cell needs a quad and the rates have no meaning.
+template <bool MIXED>
+__device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalRep& e, const CellRec& rec,
+                                            uint32_t cell, uint32_t period, int32_t* q, bool& done) {
+    using M = typename std::conditional<MIXED, MathFast, MathOf<float>>::type;
+    uint32_t k0 = (uint32_t)e.seed, k1 = (uint32_t)(e.seed >> 32);
+    asm volatile("" : "+s"(k0), "+s"(k1));   // as in quad_words
+    float mu = 1.f;
+    if (e.sigma != 0.f) {
+        const uint4 n = philox4x32_10(make_uint4(cell, period, e.rep, 0u), k0, k1);
+        mu = noise_of<float, M>(n.x, n.y, e.sigma);
+    }
+    const CellRates<float> cr = lane_cell_rates<M>(x, rec, done);
+    if constexpr (MIXED) done = done && !cr.edge;
+    bool faint = false;
+    if (e.hfi_min > 0.f) {
+        const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr) * mu);
+        const double hm = (double)e.hfi_min;
+        if constexpr (MIXED) done = done && fabs(hfi - hm) > kMixMarginH * hm;
+        faint = !(hfi >= hm);
+    }
+    float x8[8];
+    lane_axis_rates<M>(cr, mu, x8);
+    uint32_t w[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = 0x80000000u;   // 1/2 as a 24-bit fraction
+    if (e.rounding != 0) {
+        const uint4 ua = philox4x32_10(make_uint4(cell, period, e.rep, 1u), k0, k1);
+        const uint4 ub = philox4x32_10(make_uint4(cell, period, e.rep, 2u), k0, k1);
+        w[0] = ua.x, w[1] = ua.y, w[2] = ua.z, w[3] = ua.w;
+        w[4] = ub.x, w[5] = ub.y, w[6] = ub.z, w[7] = ub.w;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float u = unit24<float>(w[k]);
+        if constexpr (MIXED) q[k] = quantise_mixed(x8[k], u, done);
+        else q[k] = quantise<float>(x8[k], u);
+    }
+    return faint;
+}
+
+// head_rate with the context in LDS, out of line: used only where an
+// ignition threshold is set.
+template <typename R>
+static inline __device__ __attribute__((noinline)) R head_rate_lds(const EvalLds<R>* x, const EvalLds<double>* x64,
+                                                            const EvalRep* e, const CellRec* cells, uint32_t cell,
+                                                            uint32_t period) {
+    const CellRec rec = cells[cell];
+    const LandR<R> L{x->L.pc_w, x->L.cf, (R)0, x->L.pdf_w, x->L.fme_r, x->L.csi};
+    const LandR<double> L64{x64->L.pc_w, x64->L.cf, 0.0, x64->L.pdf_w, x64->L.fme_r, x64->L.csi};
+    const CellRates<R> cr = cell_rates<R>(x->coef, x64->coef, rec, x->row, x64->row, L, L64);
+    return cr.h * noise_mult<R>(e->seed, cell, period, e->rep, (R)e->sigma);
 }
 
 }  // namespace c2f

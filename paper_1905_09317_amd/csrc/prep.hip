@@ -76,7 +76,8 @@ __global__ void cellrec_kernel(const uint8_t* __restrict__ fuel, const int16_t* 
         const int f = fuel[i];
         rec.info = (uint32_t)f | (mask << 8);
         rec.grad = (uint32_t)(uint16_t)(int16_t)gx | ((uint32_t)(uint16_t)(int16_t)gn << 16);
-        rec.pad[0] = rec.pad[1] = 0u;
+        rec.ux = rec.uy = 0.f;
+        if ((gx | gn) != 0) upslope_unit<float>(gx, gn, rec.ux, rec.uy);
         rec.sfc = 1.0;
         rec.sfd = 1.0;
         if ((gx | gn) != 0 && f != kNonFuel) {
@@ -321,25 +322,21 @@ __global__ void eval_ros_kernel(EvalArgs a) {
             if (a.raz) a.raz[i] = 0;
             if (a.cfb) a.cfb[i] = 0;
             if (a.hfi) a.hfi[i] = 0;
-            for (int k = 0; k < 8; ++k) {
+            for (int k = 0; k < 8; ++k)
                 if (a.x8) a.x8[(size_t)i * 8 + k] = 0;
-                if (a.q8) a.q8[(size_t)i * 8 + k] = 0;
-            }
             continue;
         }
         const CellRates<R> cr = cell_rates<R>(X.coef, X.coef64, rec, X.rows + ro, X.rows64 + ro, X.L, X.L64);
         const R mu = noise_mult<R>(a.seed, (uint32_t)i, (uint32_t)a.period, a.rep, (R)a.sigma);
         R x[8];
         axis_rates<R>(cr, mu, x);
-        int32_t q[8];
-        axis_q<R>(X, rec, (uint32_t)i, (uint32_t)a.period, q);
         if (a.hros) a.hros[i] = (double)(cr.h * mu);
         if (a.bros) a.bros[i] = (double)(cr.b * mu);
         if (a.fros) a.fros[i] = (double)((cr.h + cr.b) / ((R)2 * cr.lb) * mu);
         if (a.lb) a.lb[i] = (double)cr.lb;
         if (a.cfb || a.hfi) {
             R cfb = (R)0;
-            const R hfi = head_intensity<R>(cr, f, X.rows + ro, X.L, &cfb) * mu;
+            const R hfi = head_intensity(cr, f, X.rows + ro, X.L, &cfb) * mu;
             if (a.cfb) a.cfb[i] = (double)cfb;
             if (a.hfi) a.hfi[i] = (double)hfi;
         }
@@ -351,10 +348,42 @@ __global__ void eval_ros_kernel(EvalArgs a) {
             }
             a.raz[i] = az;
         }
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 8; ++k)
             if (a.x8) a.x8[(size_t)i * 8 + k] = (double)x[k];
-            if (a.q8) a.q8[(size_t)i * 8 + k] = q[k];
-        }
+    }
+}
+
+// The integer rates, by the evaluation of the propagation kernel: four lanes
+// a cell, curves, weather row and landscape constants in LDS.
+template <typename R>
+__global__ __launch_bounds__(256) void eval_q8_kernel(EvalArgs a) {
+    __shared__ EvalLds<double> s_x64;
+    __shared__ EvalLds<float> s_x32;
+    __shared__ EvalRep s_e;
+    const EvalRep e{a.seed, a.rep, a.rounding, a.sigma, 0.f};
+    const int tid = (int)threadIdx.x, role = tid & 3;
+    const size_t ro = ((size_t)a.scenario * a.n_wp + a.period) * kRowLen;
+    if (tid < kNumCurves) {
+        s_x64.coef[tid] = curve_entry<double>(tid);
+        s_x32.coef[tid] = curve_entry<float>(tid);
+    }
+    if (tid < kNumFuels) {
+        load_land<double>(a.land, s_x64.L, tid);
+        load_land<float>(a.land, s_x32.L, tid);
+    }
+    if (tid < kRowLen) {
+        s_x64.row[tid] = a.table64[ro + tid];
+        s_x32.row[tid] = a.table32[ro + tid];
+    }
+    if (tid == 0) s_e = e;
+    __syncthreads();
+    for (int64_t i = (int64_t)blockIdx.x * 64 + (tid >> 2); i < a.n_cells; i += (int64_t)gridDim.x * 64) {
+        const CellRec rec = a.cells[i];
+        int32_t qa = 0, qb = 0;
+        if (rec_fuel(rec.info) != 0)
+            quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, e, &s_e, rec, (uint32_t)i, (uint32_t)a.period, role, qa, qb);
+        a.q8[(size_t)i * 8 + role] = qa;
+        a.q8[(size_t)i * 8 + role + 4] = qb;
     }
 }
 
@@ -362,6 +391,11 @@ hipError_t launch_eval_ros(int precision, const EvalArgs& a, hipStream_t s) {
     const int g = fill_grid((size_t)a.n_cells);
     if (precision == 1) hipLaunchKernelGGL(eval_ros_kernel<float>, dim3(g), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(eval_ros_kernel<double>, dim3(g), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.q8) return e;
+    const int gq = (int)(((int64_t)a.n_cells + 63) / 64 < 8192 ? ((int64_t)a.n_cells + 63) / 64 : 8192);
+    if (precision == 1) hipLaunchKernelGGL(eval_q8_kernel<float>, dim3(gq), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(eval_q8_kernel<double>, dim3(gq), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -28,9 +28,29 @@
 // Improved cells go to the period's work queue (LDS, spilling to the slot's
 // global list): each wave reserves a range with one LDS atomic, writes its
 // entries and commits the range in reservation order; waves take committed
-// chunks of up to 64 entries as soon as they are free, so no wave waits for
+// chunks of up to 16 entries as soon as they are free, so no wave waits for
 // the others between hops.  The period ends when no wave holds a chunk and
 // every reserved entry has been taken.
+//
+// Lanes a cell.  The kernel is bound by a chain of dependent passes (a hop of
+// the fire front is one) and, with many replications, by vector instructions.
+// A narrow pass gives a cell to four lanes, 16 cells a pass: each lane takes
+// two opposite axes, and the three rate curves and three random blocks of a
+// cell run side by side.  It takes about 620 vector instructions and, alone on
+// its SIMD, 3 thousand cycles of evaluation, 2 thousand of loads, 1 thousand
+// of label atomics and 1.7 thousand of appends.  A wide pass gives a cell to
+// one lane, 64 cells a pass, in about 1100 instructions, so it costs half as
+// many a cell but takes longer from a cell's arrival to its neighbours'.
+// Continuations go wide when there are more of them than the group's waves
+// take in one narrow pass, queue entries when more than 32 are waiting and the
+// idle waves could not take them all narrow.  FP64 evaluations are called from
+// narrow passes only: inlined, or called from wide ones, their constants and
+// the registers saved around the call made the loop spill.
+// Against one lane a cell throughout with inlined FP64 code (1900 instructions
+// a pass at 40 cells on average, 256 registers, 8 waves a compute unit), in ms:
+// 8192^2 x 64 replications x 72 periods 7.70 -> 4.50, 1024^2 x 2048 x 48
+// 39.1 -> 19.6, one FP32 fire on 2048^2 x 48 3.61 -> 2.23, 20 x 20 cells x 10
+// 0.24 -> 0.13.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -44,6 +64,17 @@
 namespace c2f {
 
 constexpr int32_t kNever = 0x7FFFFFFF;
+typedef __attribute__((address_space(1))) CellRec GCellRec;
+
+constexpr int kChunk = 16;   // cells a wave takes at a time, four lanes each
+// More queue entries than this may be taken as one pass of one lane each
+// (1024^2 x 2048 replications x 48 periods: 13.9 ms at 24, 32 and 47).
+constexpr int kWideMin = 32;
+
+// Had the cell not burned when it held label v (an older tag, or pending)?
+__device__ __forceinline__ bool unburned(uint32_t v, uint32_t tag) {
+    return (v >> kMinuteBits) != tag || (v & kMinuteMask) == kPendingMinute;
+}
 
 __device__ __forceinline__ uint32_t load_label(const uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -67,11 +98,11 @@ __device__ __forceinline__ int wave_reserve(bool pred, int* counter, uint64_t& m
 }
 
 template <typename T>
-__device__ __forceinline__ void append_g(bool pred, const T& val, T* glob, int64_t cap, int* counter, int* flag) {
+__device__ __forceinline__ void append_g(bool pred, const T& val, T* glob, uint32_t cap, int* counter, int* flag) {
     uint64_t m;
     const int idx = wave_reserve(pred, counter, m);
     if (pred) {
-        if ((int64_t)idx < cap) glob[idx] = val;
+        if ((uint32_t)idx < cap) glob[idx] = val;
         else *flag = 1;
     }
 }
@@ -89,107 +120,57 @@ __device__ __forceinline__ int32_t ceil_div_small(int32_t r, int32_t q) {
     return (int32_t)t;
 }
 
-// Advance cell c (label lab) through period p from minute m0 to e.  nbv[k]
-// is the label of neighbour k read at the start of the pass; rem[k] holds
-// the metres left on axis k (0 = done).  On return cand[k] is the
-// minute the fire reaches neighbour k inside p (or kNever) and rem[] the
-// metres left at the end of p for axes still worth following.  An axis is
-// dropped once its neighbour already holds a label no later candidate can
-// beat, or is pending (its ignition minute is then already determined).
-template <typename R>
-__device__ __forceinline__ int advance(const RateCtx<R>& X, const CellRec& rec, uint32_t c, int p, int32_t m0,
-                                       int32_t e, const uint32_t* nbv, uint32_t tag, int32_t* rem, int32_t* cand) {
-    const uint32_t nb = rec_nbmask(rec.info);
-    uint32_t live = 0, settled = 0;   // settled: neighbour label <= e + 1
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        cand[k] = kNever;
-        if (!((nb >> k) & 1u) || rem[k] <= 0) {
-            rem[k] = 0;
-            continue;
-        }
-        const uint32_t v = nbv[k];
-        if ((v >> kMinuteBits) == tag) {
-            const int32_t t = (int32_t)(v & kMinuteMask);
-            if (t == (int32_t)kPendingMinute || t <= m0) {
-                rem[k] = 0;
-                continue;
-            }
-            if (t <= e + 1) settled |= 1u << k;
-        }
-        live |= 1u << k;
-    }
-    int evals = 0;
-    if (live != 0u && m0 <= e) {
-        int32_t q[8];
-        const bool faint = axis_q<R>(X, rec, c, (uint32_t)p, q);
-        evals = 1;
-        if (faint) {
-            // burn-out (A5 (iv)): the head fire intensity is below the threshold
-#pragma unroll
-            for (int k = 0; k < 8; ++k) rem[k] = 0;
-            return evals;
-        }
-        if (X.burnout > 0.f) {
-            // burn-out (A5 (i)): every rate toward a burnable neighbour is
-            // below delta, so the cell spreads no further
-            int32_t qmax = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-                if ((nb >> k) & 1u) qmax = max(qmax, q[k]);
-            if ((double)qmax < (double)X.burnout) {
-#pragma unroll
-                for (int k = 0; k < 8; ++k) rem[k] = 0;
-                return evals;
-            }
-        }
-        // minutes left in p; metres left per axis are below 2^16 (at most
-        // the diagonal of a 20 km cell), so when q < r and n < r every
-        // product below fits in 32 bits
-        const int32_t n = e - m0 + 1;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (!((live >> k) & 1u)) continue;
-            const int32_t qk = q[k], r = rem[k];
-            bool reach = false;
-            int32_t step = 0;
-            if (qk > 0) {
-                if (qk >= r || n >= r) {
-                    reach = true;
-                } else {
-                    // qk < r < 2^16 and n < r: a 24-bit product
-                    step = (int32_t)__umul24((uint32_t)qk, (uint32_t)n);
-                    reach = step >= r;
-                }
-            }
-            if (reach) {
-                cand[k] = m0 + (qk >= r ? 1 : ceil_div_small(r, qk)) - 1;
-                rem[k] = 0;
-            } else {
-                rem[k] = r - step;
-                if ((settled >> k) & 1u) rem[k] = 0;   // nothing after p can beat it
-            }
-        }
-    }
-    return evals;
+// One axis of a cell advanced through the n minutes left of a period at the
+// integer rate q: rem > 0 holds the metres left and is below 2^16 (at most the
+// diagonal of a 20 km cell).  Returns the number of minutes the fire needs to
+// reach the neighbour (1..n, rem becomes 0), or 0 if it does not in this
+// period.
+__device__ __forceinline__ int32_t step_axis(int32_t q, int32_t& rem, int32_t n) {
+    const int32_t t = ceil_div_small(rem, max(q, 1));   // 1 where q >= rem
+    const bool reach = q > 0 && t <= n;
+    // q n < rem < 2^16 when the neighbour is not reached
+    rem = reach ? 0 : rem - (int32_t)__umul24((uint32_t)q, (uint32_t)n);
+    return reach ? t : 0;
 }
 
-// At least 2 waves per SIMD (<= 256 VGPRs).  A tighter bound (4 waves,
-// 128 VGPRs) doubles the resident replications but spills several hundred
-// bytes per lane to scratch in every pass, and measured slower; a 768-thread
-// group needs 3 waves per SIMD (168 VGPRs) and a 1024-thread one 4 (128).
+__device__ __forceinline__ CellRec load_rec(const GCellRec* p) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) const u32x4 g4;
+    const u32x4 a = ((g4*)p)[0], b = ((g4*)p)[1];
+    CellRec r;
+    r.info = a.x;
+    r.grad = a.y;
+    r.ux = __uint_as_float(a.z);
+    r.uy = __uint_as_float(a.w);
+    r.sfc = __hiloint2double((int)b.y, (int)b.x);
+    r.sfd = __hiloint2double((int)b.w, (int)b.z);
+    return r;
+}
+
+// Is an axis with rem metres left still worth following from minute m0?  d is
+// the neighbour's label less the tag's part: its minute if it has burned in
+// this replication, kPendingMinute if it waits for a passing rate (its
+// ignition minute is then already determined), more if it has not burned.  No
+// once the neighbour holds a label no later candidate can beat.
+__device__ __forceinline__ bool axis_live(int32_t rem, uint32_t d, int32_t m0) {
+    return rem > 0 && d > (uint32_t)m0 && d != kPendingMinute;
+}
+
+// 4 waves per SIMD (128 VGPRs; 107 are used).  With narrow passes alone, 5, 6
+// and 8 waves spilled 80, 144 and 208 bytes per lane and were 4, 22 and 60 %
+// slower on 8192^2 x 64 replications x 72 periods at 1024 threads.
 template <typename R, int BLOCK>
-__global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restrict__ jobs, int n_jobs,
+__global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restrict__ jobs, int n_jobs,
                                                           int total_items, Slots slots,
                                                           RunCounters* __restrict__ rc) {
-    constexpr int LCAP = BLOCK <= 64 ? 512 : (BLOCK <= 128 ? 1024 : (BLOCK <= 256 ? 2048 : 4096));
-    constexpr int LQ = 2 * LCAP;   // LDS part of the period queue
+    constexpr int LQ = BLOCK <= 64 ? 1024 : (BLOCK <= 128 ? 2048 : 4096);   // LDS part of the period queue
     __shared__ uint2 s_Q[LQ];
     __shared__ int s_res, s_commit;   // queue entries reserved, committed (in order)
     // queue entries taken (high 32 bits) and waves holding a chunk (low 32),
     // one word so that taking a chunk and becoming a holder is one step
     __shared__ unsigned long long s_hb;
     __shared__ int s_nC[2], s_nP[2];
+    __shared__ int s_ctake;           // continuations taken
     __shared__ int s_item, s_flag;
     __shared__ uint32_t s_tag;
     __shared__ int s_scen, s_ign;
@@ -200,33 +181,31 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
     // (leave the period loop after this period).
     __shared__ int s_refill, s_stop;
     __shared__ unsigned long long s_cnt[kNumCounters];
-    __shared__ CoefR<R> s_coef[kNumFuels];
-    __shared__ CoefR<double> s_coef64[kNumFuels];
-    __shared__ CoefR<float> s_coef32[kNumFuels];
-    // the weather rows of the period being propagated (FP64, and FP32 where
-    // the context evaluates in FP32 or tries FP32 first), staged at the
-    // start of each period so that every evaluation reads them from LDS
-    __shared__ double s_row64[kRowLen];
-    __shared__ float s_row32[kRowLen];
-    // the landscape's critical surface intensities, per fuel
-    __shared__ double s_csi64[kNumFuels];
-    __shared__ float s_csi32[kNumFuels];
+    // what the evaluations read: the curves, the weather rows of the period
+    // being propagated (staged at the start of each period) and the
+    // landscape's constants, in both precisions
+    __shared__ EvalLds<double> s_x64;
+    __shared__ EvalLds<float> s_x32;
+    __shared__ EvalRep s_e;
 
+    constexpr int NW = BLOCK / 64;
     const int tid = threadIdx.x;
     const int slot = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int quad = (tid & 63) >> 2, role = tid & 3;   // the lane's cell of a chunk, its axes there
     __builtin_amdgcn_s_setprio(1);
-    if (tid < kNumFuels) {
-        s_coef[tid] = coef_table<R>()[tid];
-        s_coef64[tid] = coef_table<double>()[tid];
-        s_coef32[tid] = coef_table<float>()[tid];
+    if (tid < kNumCurves) {
+        s_x64.coef[tid] = curve_entry<double>(tid);
+        s_x32.coef[tid] = curve_entry<float>(tid);
     }
     uint32_t* __restrict__ plane = slots.planes + (size_t)slot * (size_t)slots.plane_cells;
     const int64_t stride = slots.list_cap;   // entries allocated per list
-    const int64_t cap = slots.list_limit;    // entries used per list (<= stride)
+    const uint32_t cap = (uint32_t)slots.list_limit;   // entries used per list (<= stride, <= 2^30)
     uint8_t* lb = slots.lists + (size_t)slot * (size_t)stride * (size_t)kSlotListBytesPerEntry;
     uint2* const gQ = (uint2*)lb;        // global part of the period queue: 2 x cap entries
-    Cont* const gC[2] = {(Cont*)(lb + 16 * stride), (Cont*)(lb + 16 * stride) + stride};
-    uint32_t* const gP[2] = {(uint32_t*)(lb + 64 * stride), (uint32_t*)(lb + 64 * stride) + stride};
+    // continuation and pending lists, one of each pair current
+    auto gC = [&](int w) __attribute__((always_inline)) { return (Cont*)(lb + 16 * stride) + (w ? stride : 0); };
+    auto gP = [&](int w) __attribute__((always_inline)) { return (uint32_t*)(lb + 64 * stride) + (w ? stride : 0); };
 
     for (int taken = 0;; ++taken) {
         // With deferred dense outputs (item_slot set) a slot's plane must
@@ -259,18 +238,20 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
         const int cols = job.cols;
         const int rows = job.rows;
         const int P = job.period_min;
-        const CellRec* __restrict__ cells = job.cells;
+        // a global pointer: loads through a generic one wait on LDS as well
+        const GCellRec* const cells = (const GCellRec*)job.cells;
         const bool use_thr = job.threshold > 0.0f;
         const R thr = (R)job.threshold;
-        const int32_t D[8] = {job.d_orth, job.d_diag, job.d_orth, job.d_diag,
-                              job.d_orth, job.d_diag, job.d_orth, job.d_diag};
-        const int32_t off[8] = {1, 1 - cols, -cols, -cols - 1, -1, cols - 1, cols, cols + 1};
+        // the lane's axes `role` and `role` + 4: centre distance, and the
+        // neighbours' index offsets offk and -offk
+        const int32_t Dk = (role & 1) ? job.d_diag : job.d_orth;
+        const int32_t offk = role == 0 ? 1 : role == 1 ? 1 - cols : role == 2 ? -cols : -cols - 1;
         const uint32_t last_cell = (uint32_t)((int64_t)rows * cols - 1);
 
         // ------------------------------------------- replication set-up
         if (tid < kNumFuels) {
-            s_csi64[tid] = job.land->csi64[tid];
-            s_csi32[tid] = job.land->csi32[tid];
+            load_land<double>(job.land, s_x64.L, tid);
+            load_land<float>(job.land, s_x32.L, tid);
         }
         if (tid == 0) {
             const uint32_t prev = slots.tags[slot];
@@ -279,6 +260,7 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
             s_res = s_commit = 0;
             s_hb = 0ull;
             s_nC[0] = s_nC[1] = s_nP[0] = s_nP[1] = 0;
+            s_ctake = 0;
             s_flag = 0;
             s_stop = 0;
             for (int k = 0; k < kNumCounters; ++k) s_cnt[k] = 0;
@@ -286,6 +268,7 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
             rep_draws(job, rep, scen, ign);
             s_scen = scen;
             s_ign = ign;
+            s_e = EvalRep{job.seed, rep, job.rounding, job.sigma, job.hfi_min};
         }
         __syncthreads();
         if (s_refill) {
@@ -311,37 +294,27 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
         const uint32_t tag = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_tag);
         const int scen_r = __builtin_amdgcn_readfirstlane(s_scen);
         const uint32_t pendv = (tag << kMinuteBits) | kPendingMinute;
-        RateCtx<R> X;
-        X.coef = s_coef;
-        X.coef64 = s_coef64;
-        X.L = land_consts<R>(job.land);
-        X.L64 = land_consts<double>(job.land);
-        if constexpr (sizeof(R) == 8) X.L.csi = (const R*)s_csi64;
-        else X.L.csi = (const R*)s_csi32;
-        X.L64.csi = s_csi64;
         const size_t so = (size_t)scen_r * job.n_wp * kRowLen;
         const double* const g_rows64 = job.table64 + so;
-        const float* const g_rows32 =
-            sizeof(R) == 4 ? (const float*)job.table + so : (job.table32 ? job.table32 + so : nullptr);
-        if constexpr (sizeof(R) == 8) X.rows = (const R*)s_row64;
-        else X.rows = (const R*)s_row32;
-        X.rows64 = s_row64;
-        X.row_stride = 0;
-        X.coef32 = s_coef32;
-        X.L32 = land_consts<float>(job.land);
-        X.L32.csi = s_csi32;
-        X.rows32 = g_rows32 ? s_row32 : nullptr;
-        X.seed = job.seed;
-        X.sigma = (R)job.sigma;
-        X.rounding = job.rounding;
-        X.rep = rep;
-        X.burnout = job.burnout;
-        X.hfi_min = job.hfi_min;
+        const float* const g_rows32 = job.table32 + so;
+        const EvalRep erep{job.seed, rep, job.rounding, job.sigma, job.hfi_min};
+        const float burnout = job.burnout;
+        // a global pointer: through a generic one each count would wait on
+        // LDS and memory both
+        typedef __attribute__((address_space(1))) uint32_t gu32;
+        gu32* const count = (gu32*)job.count;
+        auto count_one = [&](uint32_t j) __attribute__((always_inline)) {
+            (void)__hip_atomic_fetch_add(count + j, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        // the receiving cell's ignition test: its head rate exceeds the threshold
+        auto ignites = [&](uint32_t j, int p) __attribute__((always_inline)) {
+            if constexpr (sizeof(R) == 8) return head_rate_lds<double>(&s_x64, &s_x64, &s_e, job.cells, j, (uint32_t)p) > thr;
+            else return head_rate_lds<float>(&s_x32, &s_x64, &s_e, job.cells, j, (uint32_t)p) > thr;
+        };
 
         uint32_t c_entries = 0, c_conts = 0, c_evals = 0, c_cand = 0, c_impr = 0, c_ign = 0, c_rounds = 0;
         int max_list = 0;
         int cc = 0, pc = 0;   // which buffer of each list pair is current
-        const int64_t qcap = (int64_t)LQ + 2 * cap;   // queue entries per period
 
         // Append one entry per lane where `pred` holds: one reservation per
         // wave, entries written, then the range committed in reservation
@@ -357,7 +330,7 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
         };
         auto q_put = [&](int idx, uint2 val) __attribute__((always_inline)) {
             if (idx < LQ) s_Q[idx] = val;
-            else if ((int64_t)(idx - LQ) < 2 * cap) gQ[idx - LQ] = val;
+            else if ((uint32_t)(idx - LQ) < 2 * cap) gQ[idx - LQ] = val;
             else s_flag = 1;
         };
         auto q_append1 = [&](bool pred, uint2 val) __attribute__((always_inline)) {
@@ -390,7 +363,7 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
                         const uint32_t v = (tag << kMinuteBits) | (uint32_t)(job.seeds[k].y * P);
                         const uint32_t old = atomicMin(&plane[c], v);
                         if (v < old) {
-                            if ((old >> kMinuteBits) != tag || (old & kMinuteMask) == kPendingMinute) {
+                            if (unburned(old, tag)) {
                                 ++c_ign;
                                 if (job.count) atomicAdd(&job.count[c], 1u);
                             }
@@ -406,8 +379,8 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
             if (!burning_period(job, p)) continue;
             // every wave has left the previous period (its end barriers)
             for (int i = tid; i < kRowLen; i += BLOCK) {
-                s_row64[i] = g_rows64[(size_t)p * kRowLen + i];
-                if (g_rows32) s_row32[i] = g_rows32[(size_t)p * kRowLen + i];
+                s_x64.row[i] = g_rows64[(size_t)p * kRowLen + i];
+                s_x32.row[i] = g_rows32[(size_t)p * kRowLen + i];
             }
             __syncthreads();
             const int32_t s = p * P + 1;   // first minute of period p
@@ -424,249 +397,421 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
             // Pending cells ignite at the start of p if their rate now passes;
             // the new labels join this period's queue.
             {
-                const int nP = (int)min((int64_t)s_nP[pc], cap);
+                const int nP = min(s_nP[pc], (int)cap);
                 for (int base = 0; base < nP; base += BLOCK) {
                     const int i = base + tid;
                     bool act = i < nP;
                     uint32_t j = 0;
                     if (act) {
-                        j = gP[pc][i];
+                        j = gP(pc)[i];
                         act = load_label(&plane[j]) == pendv;
                     }
                     bool ok = false;
                     if (act) {
-                        const CellRec rj = cells[j];
                         ++c_evals;
-                        ok = head_rate<R>(X, rj, j, (uint32_t)p) > thr;
+                        ok = ignites(j, p);
                     }
                     bool improved = false, first = false;
                     const uint32_t v = (tag << kMinuteBits) | (uint32_t)s;
                     if (ok) {
                         const uint32_t old = atomicMin(&plane[j], v);
                         improved = v < old;
-                        first = improved && ((old >> kMinuteBits) != tag || (old & kMinuteMask) == kPendingMinute);
-                        if (first && job.count) atomicAdd(&job.count[j], 1u);
+                        first = improved && unburned(old, tag);
+                        if (first && count) count_one(j);
                     }
-                    c_impr += improved;
-                    c_ign += first;
+                    c_impr += (uint32_t)__popcll(__ballot(improved));
+                    c_ign += (uint32_t)__popcll(__ballot(first));
                     q_append1(improved, make_uint2(j, v));
-                    append_g(act && !ok, j, gP[pc ^ 1], cap, &s_nP[pc ^ 1], &s_flag);
+                    append_g(act && !ok, j, gP(pc ^ 1), cap, &s_nP[pc ^ 1], &s_flag);
                 }
             }
-            // Advance one entry per lane: the continuations of p-1 from the
-            // start of p (conts), or a cell whose arrival improved inside p
-            // from that minute.  Improvements are appended to the queue, axes
-            // still travelling at the end of p to the next continuation list.
-            auto process = [&](bool act, uint32_t c, uint32_t lab, int32_t* rem, bool conts) __attribute__((always_inline)) {
-                int32_t cand[8];
-                uint32_t nbv[8];
-                CellRec rec;
-                rec.info = 0;
-                if (act) {
-                    // issue every load of the entry at once: own label,
-                    // cell record and the labels of the 8 neighbours.  A
-                    // neighbour outside the grid is read at an index clamped
-                    // into the plane (an index below 0 wraps to a large
-                    // unsigned value and clamps too) and never used: the
-                    // record's neighbour mask (in-grid burnable cells)
-                    // excludes its axis.  Grids hold fewer than 2^31 cells.
-                    const uint32_t own = load_label(&plane[c]);
-                    rec = cells[c];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) nbv[k] = plane[min(c + (uint32_t)off[k], last_cell)];
-                    act = own == lab;
-                }
-                bool keep = false;
-                if (act) {
-                    // a cell lit before p (an ignition waiting out the hours
-                    // outside the burning window) advances from p's start
-                    const int32_t m0 = conts ? s : max((int32_t)(lab & kMinuteMask) + 1, s);
-                    c_evals += advance<R>(X, rec, c, p, m0, e, nbv, tag, rem, cand);
-                    keep = (rem[0] | rem[1] | rem[2] | rem[3] | rem[4] | rem[5] | rem[6] | rem[7]) != 0;
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        cand[k] = kNever;
-                        rem[k] = 0;
-                    }
-                }
-                // offer the candidates: atomicMin of real labels, or a
-                // pending mark where the neighbour's rate is below the
-                // threshold.  All atomics are issued before any result is
-                // used so that their latencies overlap.
-                uint32_t hasm = 0, pendm = 0, impr = 0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) hasm |= (act && cand[k] != kNever) ? (1u << k) : 0u;
-                if (use_thr) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        if (!((hasm >> k) & 1u)) continue;
-                        const uint32_t j = (uint32_t)((int64_t)c + off[k]);
-                        const CellRec rj = cells[j];
-                        ++c_evals;
-                        if (!(head_rate<R>(X, rj, j, (uint32_t)p) > thr)) pendm |= 1u << k;
-                    }
-                }
-                uint32_t old[8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    old[k] = 0u;
-                    if ((hasm >> k) & 1u) {
-                        const uint32_t v = ((pendm >> k) & 1u) ? pendv : (tag << kMinuteBits) | (uint32_t)cand[k];
-                        old[k] = atomicMin(&plane[(int64_t)c + off[k]], v);
-                    }
-                }
-                uint32_t newpend = 0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    if (!((hasm >> k) & 1u)) continue;
-                    if ((pendm >> k) & 1u) {
-                        if (old[k] > pendv) newpend |= 1u << k;
+            // The waves' loop over the period's work: chunks of up to 16
+            // cells, four lanes a cell.  First the continuations of p-1 from
+            // the start of p, last listed first: the cells listed last were
+            // lit latest in p-1, at the front of the fire, and tend to start
+            // the longest chains of p, which then reach the queue in the
+            // first rounds.  Then label correcting over the period's queue:
+            // cells whose arrival improved inside p, advanced from that
+            // minute.  Labels are a least fixed point whatever the order.  A
+            // wave waiting for entries drops to the lowest issue priority, so
+            // that its polling takes no issue slots from the waves working on
+            // the chain.
+            const int n_conts = min(s_nC[cc], (int)cap);
+            if (n_conts > max_list) max_list = n_conts;
+            bool conts = true;
+            const int csize = n_conts > kChunk * NW && !use_thr ? 64 : kChunk;
+            int cbase = wave * csize;   // the first chunk of continuations by wave, later ones from s_ctake
+            uint64_t redo = 0;   // lanes of the last one-lane pass whose cells a quad takes
+            int base = 0;
+            for (;;) {
+                int cnt = 0;
+                const bool again = redo != 0;
+                if (again) {
+                    cnt = min((int)__popcll(redo), kChunk);
+                } else if (conts) {
+                    if (cbase >= n_conts) {
+                        conts = false;
+                        if (__lane_id() == 0) atomicAdd(&s_hb, ~0ull);   // no longer a holder
                         continue;
                     }
-                    const uint32_t v = (tag << kMinuteBits) | (uint32_t)cand[k];
-                    if (v < old[k]) {
-                        impr |= 1u << k;
-                        if ((old[k] >> kMinuteBits) != tag || (old[k] & kMinuteMask) == kPendingMinute) {
-                            ++c_ign;
-                            if (job.count) atomicAdd(&job.count[(int64_t)c + off[k]], 1u);
-                        }
-                    }
-                }
-                c_cand += __popc(hasm);
-                // append the wave's improved neighbours axis by axis: one
-                // ballot per axis gives each lane its place in the range
-                c_impr += __popc(impr);
-                uint64_t am[8];
-                int wtot = 0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    am[k] = __ballot((impr >> k) & 1u);
-                    wtot += (int)__popcll(am[k]);
-                }
-                if (wtot > 0) {
-                    int wbase = 0;
-                    if (__lane_id() == 0) wbase = atomicAdd(&s_res, wtot);
-                    int idx = lane_value(wbase, 0);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        if ((impr >> k) & 1u)
-                            q_put(idx + wave_rank(am[k]),
-                                  make_uint2((uint32_t)((int64_t)c + off[k]), (tag << kMinuteBits) | (uint32_t)cand[k]));
-                        idx += (int)__popcll(am[k]);
-                    }
-                    q_commit(lane_value(wbase, 0), wtot);
-                }
-                if (use_thr) {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        append_g(((newpend >> k) & 1u) != 0u, (uint32_t)((int64_t)c + off[k]), gP[pc ^ 1], cap,
-                                 &s_nP[pc ^ 1], &s_flag);
-                }
-                // axes still travelling at the end of p continue in p+1
-                Cont ct;
-                ct.c = c;
-                ct.label = lab;
-#pragma unroll
-                for (int h = 0; h < 4; ++h) ct.rem[h] = (uint32_t)rem[2 * h] | ((uint32_t)rem[2 * h + 1] << 16);
-                append_g(keep, ct, gC[cc ^ 1], cap, &s_nC[cc ^ 1], &s_flag);
-            };
-
-            // Continuations of p-1, advanced from the start of p, last
-            // listed first: the cells listed last were lit latest in p-1, at
-            // the front of the fire, and tend to start the longest chains of
-            // p, which then reach the queue in the first rounds.  Labels are
-            // a least fixed point whatever the order.
-            {
-                const int n = (int)min((int64_t)s_nC[cc], cap);
-                if (n > max_list) max_list = n;
-                for (int base = 0; base < n; base += BLOCK) {
-                    const int i = base + tid;
-                    const bool act = i < n;
-                    uint32_t c = 0, lab = 0;
-                    int32_t rem[8];
-                    if (act) {
-                        const Cont ct = gC[cc][n - 1 - i];
-                        c = ct.c;
-                        lab = ct.label;
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            rem[2 * h] = (int32_t)(ct.rem[h] & 0xFFFFu);
-                            rem[2 * h + 1] = (int32_t)(ct.rem[h] >> 16);
-                        }
-                        ++c_conts;
-                    }
-                    process(act, c, lab, rem, true);
-                }
-            }
-            if (__lane_id() == 0) atomicAdd(&s_hb, ~0ull);   // no longer a holder
-
-            // label correcting over the period's queue.  A wave waiting for
-            // entries drops to the lowest issue priority, so that its polling
-            // takes no issue slots from the waves working on the chain.
-            for (;;) {
-                int base = 0, cnt = 0;
-                bool done = false;
-                __builtin_amdgcn_s_setprio(0);
-                if (__lane_id() == 0) {
-                    for (;;) {
-                        if (__hip_atomic_load(&s_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                            done = true;
-                            break;
-                        }
-                        const unsigned long long hb =
-                            __hip_atomic_load(&s_hb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        const int h = (int)(hb >> 32), holders = (int)(uint32_t)hb;
-                        const int cm = __hip_atomic_load(&s_commit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (h < cm) {
-                            const int take = min(64, cm - h);
-                            const unsigned long long nhb = ((unsigned long long)(uint32_t)(h + take) << 32) |
-                                                           (unsigned long long)(uint32_t)(holders + 1);
-                            if (atomicCAS(&s_hb, hb, nhb) == hb) {
-                                base = h;
-                                cnt = take;
+                    base = cbase;
+                    cnt = min(csize, n_conts - base);
+                } else {
+                    bool done = false;
+                    base = 0;
+                    __builtin_amdgcn_s_setprio(0);
+                    if (__lane_id() == 0) {
+                        for (;;) {
+                            if (__hip_atomic_load(&s_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                                done = true;
                                 break;
                             }
-                            continue;
+                            const unsigned long long hb =
+                                __hip_atomic_load(&s_hb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            const int h = (int)(hb >> 32), holders = (int)(uint32_t)hb;
+                            const int cm =
+                                __hip_atomic_load(&s_commit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            if (h < cm) {
+                                const int avail = cm - h;
+                                const bool many = avail > kWideMin && avail > kChunk * (NW - holders) && !use_thr;
+                                const int take = min(many ? 64 : kChunk, avail);
+                                const unsigned long long nhb = ((unsigned long long)(uint32_t)(h + take) << 32) |
+                                                               (unsigned long long)(uint32_t)(holders + 1);
+                                if (atomicCAS(&s_hb, hb, nhb) == hb) {
+                                    base = h;
+                                    cnt = take;
+                                    break;
+                                }
+                                continue;
+                            }
+                            // finished when no wave holds a chunk (so none can
+                            // append) and every reserved entry has been taken
+                            const int rs =
+                                __hip_atomic_load(&s_res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                            if (holders == 0 && h == cm && cm == rs) {
+                                done = true;
+                                break;
+                            }
+                            __builtin_amdgcn_s_sleep(1);
                         }
-                        // finished when no wave holds a chunk (so none can
-                        // append) and every reserved entry has been taken
-                        const int rs = __hip_atomic_load(&s_res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (holders == 0 && h == cm && cm == rs) {
-                            done = true;
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(1);
                     }
+                    base = lane_value(base, 0);
+                    cnt = lane_value(cnt, 0);
+                    done = lane_value((int)done, 0) != 0;
+                    __builtin_amdgcn_s_setprio(1);
+                    if (done) break;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    ++c_rounds;
                 }
-                base = lane_value(base, 0);
-                cnt = lane_value(cnt, 0);
-                done = lane_value((int)done, 0) != 0;
-                __builtin_amdgcn_s_setprio(1);
-                if (done) break;
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                ++c_rounds;
-                const int i = base + __lane_id();
-                bool act = __lane_id() < cnt && (int64_t)i < qcap;
-                uint32_t c = 0, lab = 0;
-                int32_t rem[8];
-                if (act) {
-                    uint2 ent;
-                    if (i < LQ) {
-                        ent = s_Q[i];
-                    } else {
-                        const uint64_t v = __hip_atomic_load((const uint64_t*)&gQ[i - LQ], __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_AGENT);
-                        ent = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+
+                if (!again) {
+                    if (conts) c_conts += (uint32_t)cnt;
+                    else c_entries += (uint32_t)cnt;
+                }
+                if (cnt > kChunk) {
+                    // one lane a cell; cells that need FP64 are set aside in
+                    // `redo` for quads
+                    const int lane = (int)__lane_id();
+                    const int i = base + lane;
+                    bool act = lane < cnt && (conts || i < LQ || (uint32_t)(i - LQ) < 2 * cap);
+                    uint32_t c = 0, lab = 0;
+                    uint32_t rem[4] = {0u, 0u, 0u, 0u};   // metres left, axis k low and k + 4 high
+                    if (act) {
+                        if (conts) {
+                            const uint2* ct = (const uint2*)(gC(cc) + (n_conts - 1 - i));
+                            const uint2 a = ct[0], r0 = ct[1], r1 = ct[2];
+                            c = a.x;
+                            lab = a.y;
+                            rem[0] = r0.x, rem[1] = r0.y, rem[2] = r1.x, rem[3] = r1.y;
+                        } else {
+                            uint2 ent;
+                            if (i < LQ) {
+                                ent = s_Q[i];
+                            } else {
+                                const uint64_t v = __hip_atomic_load((const uint64_t*)&gQ[i - LQ], __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT);
+                                ent = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+                            }
+                            c = ent.x;
+                            lab = ent.y;
+                            rem[0] = rem[2] = (uint32_t)job.d_orth * 0x10001u;
+                            rem[1] = rem[3] = (uint32_t)job.d_diag * 0x10001u;
+                        }
                     }
-                    c = ent.x;
-                    lab = ent.y;
+                    const int off[4] = {1, 1 - cols, -cols, -cols - 1};
+                    CellRec rec;
+                    rec.info = rec.grad = 0u;
+                    rec.ux = rec.uy = 0.f;
+                    rec.sfc = rec.sfd = 1.0;
+                    uint32_t v[8];
+                    uint32_t own = 0;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) rem[k] = D[k];
-                    ++c_entries;
+                    for (int k = 0; k < 8; ++k) v[k] = 0u;
+                    if (act) {
+                        own = load_label(&plane[c]);
+                        rec = load_rec(cells + c);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            v[k] = plane[min(c + (uint32_t)off[k], last_cell)];
+                            v[k + 4] = plane[min(c - (uint32_t)off[k], last_cell)];
+                        }
+                    }
+                    act = act && own == lab;
+                    const int32_t m0 = max((int32_t)(lab & kMinuteMask) + 1, s);
+                    const uint32_t nb = act ? rec_nbmask(rec.info) : 0u;
+                    uint32_t settled = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t dA = v[k] - (tag << kMinuteBits), dB = v[k + 4] - (tag << kMinuteBits);
+                        const bool a = ((nb >> k) & 1u) && axis_live((int32_t)(rem[k] & 0xFFFFu), dA, m0);
+                        const bool b = ((nb >> (k + 4)) & 1u) && axis_live((int32_t)(rem[k] >> 16), dB, m0);
+                        rem[k] = (a ? rem[k] & 0xFFFFu : 0u) | (b ? rem[k] & 0xFFFF0000u : 0u);
+                        settled |= (dA <= (uint32_t)(e + 1) ? 1u << k : 0u) | (dB <= (uint32_t)(e + 1) ? 16u << k : 0u);
+                    }
+                    const bool want = (rem[0] | rem[1] | rem[2] | rem[3]) != 0u && m0 <= e;
+                    int32_t t[8];   // minutes to the neighbour, 0 = not reached in p
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) t[k] = 0;
+                    if (__any(want)) {
+                        int32_t q[8];
+                        bool done;
+                        bool out = lane_axis_q<sizeof(R) == 8>(s_x32, erep, rec, c, (uint32_t)p, q, done);
+                        redo = __ballot(want && !done);
+                        if (want && !done) rem[0] = rem[1] = rem[2] = rem[3] = 0u;
+                        if (want && done) {
+                            ++c_evals;
+                            if (burnout > 0.f) {
+                                int32_t qm = 0;
+#pragma unroll
+                                for (int k = 0; k < 8; ++k) qm = max(qm, (nb >> k) & 1u ? q[k] : 0);
+                                out = out || (double)qm < (double)burnout;
+                            }
+                            const int32_t n = e - m0 + 1;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                int32_t rA = out ? 0 : (int32_t)(rem[k] & 0xFFFFu), rB = out ? 0 : (int32_t)(rem[k] >> 16);
+                                if (rA > 0) t[k] = step_axis(q[k], rA, n);
+                                if (rB > 0) t[k + 4] = step_axis(q[k + 4], rB, n);
+                                if ((settled >> k) & 1u) rA = 0;
+                                if ((settled >> k) & 16u) rB = 0;
+                                rem[k] = (uint32_t)rA | ((uint32_t)rB << 16);
+                            }
+                        }
+                    }
+                    const bool keep = (rem[0] | rem[1] | rem[2] | rem[3]) != 0u;
+                    const uint32_t lab0 = (tag << kMinuteBits) | (uint32_t)(m0 - 1);   // + t: the neighbour's label
+                    uint32_t old[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        old[k] = 0u;   // not offered: nothing is below 0
+                        const uint32_t j = k < 4 ? c + (uint32_t)off[k & 3] : c - (uint32_t)off[k & 3];
+                        if (t[k] != 0) old[k] = atomicMin(&plane[j], lab0 + (uint32_t)t[k]);
+                    }
+                    uint32_t impr = 0, first = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const bool i_k = lab0 + (uint32_t)t[k] < old[k];
+                        impr |= i_k ? 1u << k : 0u;
+                        first |= i_k && unburned(old[k], tag) ? 1u << k : 0u;
+                        c_cand += (uint32_t)__popcll(__ballot(t[k] != 0));
+                    }
+                    uint64_t am[8];
+                    int wtot = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        am[k] = __ballot((impr >> k) & 1u);
+                        wtot += (int)__popcll(am[k]);
+                    }
+                    const uint64_t mk = __ballot(keep);
+                    const int ktot = (int)__popcll(mk);
+                    if ((wtot | ktot) != 0) {
+                        int got = 0;
+                        if (lane < 2) got = atomicAdd(lane == 0 ? &s_res : &s_nC[cc ^ 1], lane == 0 ? wtot : ktot);
+                        const int wbase = lane_value(got, 0), kbase = lane_value(got, 1);
+                        if (wtot > 0) {
+                            int idx = wbase;
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) {
+                                const uint32_t j = k < 4 ? c + (uint32_t)off[k & 3] : c - (uint32_t)off[k & 3];
+                                if ((impr >> k) & 1u) q_put(idx + wave_rank(am[k]), make_uint2(j, lab0 + (uint32_t)t[k]));
+                                idx += (int)__popcll(am[k]);
+                            }
+                            q_commit(wbase, wtot);
+                            c_impr += (uint32_t)wtot;
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) {
+                                const uint32_t j = k < 4 ? c + (uint32_t)off[k & 3] : c - (uint32_t)off[k & 3];
+                                const bool f = (first >> k) & 1u;
+                                c_ign += (uint32_t)__popcll(__ballot(f));
+                                if (count && f) count_one(j);
+                            }
+                        }
+                        const int k = kbase + wave_rank(mk);
+                        if (keep) {
+                            if ((uint32_t)k < cap) {
+                                uint2* ct = (uint2*)(gC(cc ^ 1) + k);
+                                ct[0] = make_uint2(c, lab);
+                                ct[1] = make_uint2(rem[0], rem[1]);
+                                ct[2] = make_uint2(rem[2], rem[3]);
+                            } else {
+                                s_flag = 1;
+                            }
+                        }
+                    }
+                } else {
+                    // the quad's entry: cell, label, metres left on the lane's
+                    // two axes (a cell lit in p starts with the whole distance)
+                    int i = base + quad;
+                    if (again) {
+                        for (int j = 0; j < cnt; ++j) {
+                            if (quad == j) i = base + __ffsll((unsigned long long)redo) - 1;
+                            redo &= redo - 1;
+                        }
+                    }
+                    bool act = quad < cnt && (conts || i < LQ || (uint32_t)(i - LQ) < 2 * cap);
+                    uint32_t c = 0, lab = 0;
+                    int32_t remA = 0, remB = 0;
+                    if (act) {
+                        if (conts) {
+                            const Cont* ct = gC(cc) + (n_conts - 1 - i);
+                            const uint32_t rr = ct->rem[role];
+                            c = ct->c;
+                            lab = ct->label;
+                            remA = (int32_t)(rr & 0xFFFFu);
+                            remB = (int32_t)(rr >> 16);
+                        } else {
+                            uint2 ent;
+                            if (i < LQ) {
+                                ent = s_Q[i];
+                            } else {
+                                const uint64_t v = __hip_atomic_load((const uint64_t*)&gQ[i - LQ], __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT);
+                                ent = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+                            }
+                            c = ent.x;
+                            lab = ent.y;
+                            remA = remB = Dk;
+                        }
+                    }
+
+                    // issue every load of the entry at once: own label, cell
+                    // record and the labels of the lane's two neighbours.  A
+                    // neighbour outside the grid is read at an index clamped into
+                    // the plane (an index below 0 wraps to a large unsigned value
+                    // and clamps too) and never used: the record's neighbour mask
+                    // (in-grid burnable cells) excludes its axis.  Grids hold
+                    // fewer than 2^31 cells.
+                    CellRec rec;
+                    rec.info = 0;
+                    uint32_t vA = 0, vB = 0;
+                    const uint32_t cA = c + (uint32_t)offk, cB = c - (uint32_t)offk;
+                    if (act) {
+                        const uint32_t own = load_label(&plane[c]);
+                        rec = load_rec(cells + c);
+                        vA = plane[min(cA, last_cell)];
+                        vB = plane[min(cB, last_cell)];
+                        act = own == lab;
+                    }
+
+                    int32_t candA = kNever, candB = kNever;
+                    bool keep = false;
+                    if (act) {
+                        // a cell lit before p (a continuation, or an ignition
+                        // waiting out the hours outside the burning window)
+                        // advances from p's start
+                        const int32_t m0 = max((int32_t)(lab & kMinuteMask) + 1, s);
+                        const uint32_t nb = rec_nbmask(rec.info) >> role;
+                        const uint32_t dA = vA - (tag << kMinuteBits), dB = vB - (tag << kMinuteBits);
+                        if (!(nb & 1u) || !axis_live(remA, dA, m0)) remA = 0;
+                        if (!(nb & 16u) || !axis_live(remB, dB, m0)) remB = 0;
+                        if (quad_or((uint32_t)(remA | remB)) != 0u && m0 <= e) {
+                            int32_t qA, qB;
+                            bool out = quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, erep, &s_e, rec, c, (uint32_t)p, role, qA, qB);
+                            c_evals += role == 0;
+                            // burn-out (A5 (iv)): the head fire intensity is below
+                            // the threshold; (A5 (i)): every rate toward a burnable
+                            // neighbour is below delta.  The cell spreads no further.
+                            if (burnout > 0.f) {
+                                const int32_t qm = max(nb & 1u ? qA : 0, nb & 16u ? qB : 0);
+                                out = out || quad_or((double)qm >= (double)burnout ? 1u : 0u) == 0u;
+                            }
+                            if (out) remA = remB = 0;
+                            const int32_t n = e - m0 + 1;
+                            const int32_t tA = remA > 0 ? step_axis(qA, remA, n) : 0;
+                            const int32_t tB = remB > 0 ? step_axis(qB, remB, n) : 0;
+                            if (tA) candA = m0 + tA - 1;
+                            if (tB) candB = m0 + tB - 1;
+                            // nothing after the period can beat a label of at most e + 1
+                            if (dA <= (uint32_t)(e + 1)) remA = 0;
+                            if (dB <= (uint32_t)(e + 1)) remB = 0;
+                        }
+                        keep = quad_or((uint32_t)(remA | remB)) != 0u;
+                    }
+
+                    // offer the candidates: atomicMin of real labels, or a
+                    // pending mark where the neighbour's rate is below the
+                    // threshold.  Both atomics are issued before any result is
+                    // used so that their latencies overlap.
+                    const bool hasA = candA != kNever, hasB = candB != kNever;
+                    bool pendA = false, pendB = false;
+                    if (use_thr) {
+                        if (hasA) pendA = !ignites(cA, p);
+                        if (hasB) pendB = !ignites(cB, p);
+                        c_evals += (uint32_t)hasA + (uint32_t)hasB;
+                    }
+                    const uint32_t labA = pendA ? pendv : (tag << kMinuteBits) | (uint32_t)candA;
+                    const uint32_t labB = pendB ? pendv : (tag << kMinuteBits) | (uint32_t)candB;
+                    uint32_t oldA = 0, oldB = 0;   // not offered: nothing is below 0
+                    if (hasA) oldA = atomicMin(&plane[cA], labA);
+                    if (hasB) oldB = atomicMin(&plane[cB], labB);
+                    c_cand += (uint32_t)__popcll(__ballot(hasA)) + (uint32_t)__popcll(__ballot(hasB));
+                    const bool imprA = labA < oldA && !pendA, imprB = labB < oldB && !pendB;
+                    // improved neighbours join the queue and axes still travelling
+                    // at the end of p continue in p+1, one entry per quad: one
+                    // ballot for each gives every lane its place in the wave's
+                    // ranges, which lanes 0 and 1 reserve in one LDS instruction
+                    const uint64_t mA = __ballot(imprA), mB = __ballot(imprB), mk = __ballot(keep);
+                    const int nA = (int)__popcll(mA), wtot = nA + (int)__popcll(mB), ktot = (int)(__popcll(mk) >> 2);
+                    if ((wtot | ktot) != 0) {
+                        int got = 0;
+                        if (__lane_id() < 2)
+                            got = atomicAdd(__lane_id() == 0 ? &s_res : &s_nC[cc ^ 1], __lane_id() == 0 ? wtot : ktot);
+                        const int wbase = lane_value(got, 0), kbase = lane_value(got, 1);
+                        if (wtot > 0) {
+                            if (imprA) q_put(wbase + wave_rank(mA), make_uint2(cA, labA));
+                            if (imprB) q_put(wbase + nA + wave_rank(mB), make_uint2(cB, labB));
+                            q_commit(wbase, wtot);
+                            const bool newA = imprA && unburned(oldA, tag), newB = imprB && unburned(oldB, tag);
+                            c_impr += (uint32_t)wtot;
+                            c_ign += (uint32_t)__popcll(__ballot(newA)) + (uint32_t)__popcll(__ballot(newB));
+                            if (count) {
+                                if (newA) count_one(cA);
+                                if (newB) count_one(cB);
+                            }
+                        }
+                        const int k = kbase + (wave_rank(mk) >> 2);
+                        if (keep) {
+                            if ((uint32_t)k < cap) {
+                                Cont* ct = gC(cc ^ 1) + k;
+                                if (role == 0) *(uint2*)&ct->c = make_uint2(c, lab);
+                                ct->rem[role] = (uint32_t)remA | ((uint32_t)remB << 16);
+                            } else {
+                                s_flag = 1;
+                            }
+                        }
+                    }
+                    if (use_thr) {
+                        append_g(pendA && oldA > pendv, cA, gP(pc ^ 1), cap, &s_nP[pc ^ 1], &s_flag);
+                        append_g(pendB && oldB > pendv, cB, gP(pc ^ 1), cap, &s_nP[pc ^ 1], &s_flag);
+                    }
                 }
-                process(act, c, lab, rem, false);
-                if (__lane_id() == 0) atomicAdd(&s_hb, ~0ull);   // one holder fewer
+                if (redo != 0) continue;   // still a holder
+                if (conts) {
+                    if (__lane_id() == 0) cbase = atomicAdd(&s_ctake, csize);
+                    cbase = csize * NW + lane_value(cbase, 0);
+                } else if (__lane_id() == 0) {
+                    atomicAdd(&s_hb, ~0ull);   // one holder fewer
+                }
             }
             {
                 const int n = s_res;
@@ -684,6 +829,7 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
                 s_nC[cc] = 0;
                 s_nP[pc] = 0;
                 s_res = s_commit = 0;
+                s_ctake = 0;
                 s_hb = 0ull;
             }
             cc ^= 1;
@@ -694,13 +840,15 @@ __global__ __launch_bounds__(BLOCK, 2) void propagate_kernel(const Job* __restri
         if (s_flag && tid == 0) atomicOr(&rc->overflow, 1);
 
         // per-replication counters and outputs
-        atomicAdd(&s_cnt[kCntIgnitions], (unsigned long long)c_ign);
-        atomicAdd(&s_cnt[kCntEntries], (unsigned long long)c_entries);
-        atomicAdd(&s_cnt[kCntConts], (unsigned long long)c_conts);
-        atomicAdd(&s_cnt[kCntEvals], (unsigned long long)c_evals);
-        atomicAdd(&s_cnt[kCntCandidates], (unsigned long long)c_cand);
-        atomicAdd(&s_cnt[kCntImprovements], (unsigned long long)c_impr);
-        if (__lane_id() == 0) atomicAdd(&s_cnt[kCntRounds], (unsigned long long)c_rounds);   // chunks, per wave
+        atomicAdd(&s_cnt[kCntEvals], (unsigned long long)c_evals);   // per lane, the others per wave
+        if (__lane_id() == 0) {
+            atomicAdd(&s_cnt[kCntIgnitions], (unsigned long long)c_ign);
+            atomicAdd(&s_cnt[kCntEntries], (unsigned long long)c_entries);
+            atomicAdd(&s_cnt[kCntConts], (unsigned long long)c_conts);
+            atomicAdd(&s_cnt[kCntCandidates], (unsigned long long)c_cand);
+            atomicAdd(&s_cnt[kCntImprovements], (unsigned long long)c_impr);
+            atomicAdd(&s_cnt[kCntRounds], (unsigned long long)c_rounds);
+        }
         atomicMax(&s_cnt[kCntMaxList], (unsigned long long)max_list);
         if (slots.item_slot) {
             if (tid == 0) slots.item_slot[item] = make_int2(slot, (int)tag);

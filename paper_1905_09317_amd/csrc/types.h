@@ -38,12 +38,14 @@ constexpr int kRowLen = 64;
 //         with SF the FBP slope factor exp(3.533 (GS/100)^1.2), 10 from
 //         70 % up; 1 on flat ground
 //   sfd:  SF^(1/c) for the D-1 curve (M-1/M-2 cells only)
+//   ux, uy: upslope unit vector (gx, gn) / |(gx, gn)| in FP32, as the FP32
+//         evaluation forms it (0 on flat ground)
 // With these, the slope-adjusted spread index of a fuel with curve
 // a (1 - exp(-b ISI))^c is ISF = ln(1 - sfc (1 - exp(-b ISZ))) / -b.
 struct alignas(16) CellRec {
     uint32_t info;
     uint32_t grad;
-    uint32_t pad[2];
+    float ux, uy;
     double sfc;
     double sfd;
 };
