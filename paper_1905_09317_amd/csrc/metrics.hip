@@ -22,9 +22,6 @@
 
 namespace c2f {
 
-constexpr int kMetricBlock = 256;
-constexpr int kMetricCellsPerThread = 8;
-
 // Metrics of period t from its counts (out[t] = MSE, out[T + t] = SSIM,
 // out[2 T] = Frobenius norm of the last period).
 __device__ void period_metrics(int64_t a, int64_t b, int64_t c, int t, int T, int64_t n, double* __restrict__ out) {
@@ -74,187 +71,197 @@ __device__ void finish_block(const uint32_t* part, int base, int len, unsigned l
     if (threadIdx.x == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// counts[3 t + {0, 1, 2}] += {a, b, c} of period t = blockIdx.y over the
-// block's cells.  reference is [T][n]; arrival [n] (-1 = unburned).
-__global__ __launch_bounds__(kMetricBlock) void scar_counts_kernel(const int32_t* __restrict__ arrival,
-                                                                   const uint8_t* __restrict__ reference,
-                                                                   int64_t n, int T, int period_min,
-                                                                   unsigned long long* __restrict__ counts,
-                                                                   uint32_t* __restrict__ ticket,
-                                                                   double* __restrict__ out) {
-    const int t = (int)blockIdx.y;
-    const int64_t end = (int64_t)(t + 1) * period_min;
-    const uint8_t* __restrict__ X = reference + (size_t)t * (size_t)n;
-    const int64_t base = (int64_t)blockIdx.x * (kMetricBlock * kMetricCellsPerThread);
-    uint32_t a = 0, b = 0, c = 0;   // this wave's counts (valid in every lane)
-#pragma unroll
-    for (int k = 0; k < kMetricCellsPerThread; ++k) {
-        const int64_t i = base + (int64_t)k * kMetricBlock + threadIdx.x;
-        bool x = false, y = false;
-        if (i < n) {
-            x = X[i] != 0;
-            const int32_t m = arrival[i];
-            y = m >= 0 && (int64_t)m <= end;
-        }
-        a += (uint32_t)__popcll(__ballot(x));
-        b += (uint32_t)__popcll(__ballot(y));
-        c += (uint32_t)__popcll(__ballot(x && y));
-    }
-    __shared__ uint32_t s_cnt[3];
-    if (threadIdx.x < 3) s_cnt[threadIdx.x] = 0;
-    __syncthreads();
-    if (__lane_id() == 0) {
-        atomicAdd(&s_cnt[0], a);
-        atomicAdd(&s_cnt[1], b);
-        atomicAdd(&s_cnt[2], c);
-    }
-    finish_block(s_cnt, 3 * t, 3, counts, ticket, T, n, out);
-}
-
-// The same counts with every period streamed by each lane over CPL (4 or
-// 16) consecutive cells.  Y^t is monotone in t: cell i is in Y^t from its
+// counts[3 t + {0, 1, 2}] += {a, b, c} of every period t in the block's range,
+// streamed by each lane over 16 consecutive cells.  reference is [T][n],
+// arrival [n] (-1 = unburned).  Y^t is monotone in t: cell i is in Y^t from its
 // burn period k_i = ceil(m_i / P) - 1 on (0 for m_i = 0, never for
 // m_i < 0), so each lane computes k_i once.  Periods go in windows of 127:
 // with the bytes of kb = min(max(k_i - t_w, 0), 127) for four cells in one
 // word, ((t - t_w) * 0x01010101 | 0x80808080) - kb has bit 7 of byte u set
-// exactly when cell u is in Y^t (every byte stays in 1..254, so no borrow
-// crosses bytes); bit 7 of a byte of (((w & 0x7F..) + 0x7F..) | w) is set
+// exactly when cell u is in Y^t (every byte stays in 1..254 for t - t_w up to 126,
+// so no borrow crosses bytes; later periods of a batch are not counted); bit 7 of a byte of (((w & 0x7F..) + 0x7F..) | w) is set
 // exactly when that byte of the reference word w is nonzero.  A lane's
-// three counts (0..16 each) go packed in 10-bit fields through a DPP sum
-// over each 16-lane row (at most 256 per field) and a read of the four row
-// sums; wave sums are collected per period in LDS (12 T bytes) and added
-// to the global counts once per block.  Reference loads of kRowsBatch
-// periods are issued before any is used.  Needs n % CPL == 0, 16-byte
-// aligned arrival and CPL-byte aligned reference, T <= kRowsMaxPeriods.
+// three counts (0..16 each) go packed in 10-bit fields through DPP sums
+// over each 16-lane row (at most 256 per field), eight periods together; each
+// row adds its sums to the block's counts of the periods in LDS, one 64-bit
+// word with a field of 21 bits a count (a block counts at most 2^20 cells).
+// Reference loads of kRowsBatch (8) periods are issued before any is used.
+//
+// Bound by the reference read.  The rows of a grid of n cells start n bytes
+// apart, so unless n is a multiple of 16 a lane's 16 bytes straddle words:
+// ALIGNED = false reads them with unaligned 16-byte loads (the last lane, whose
+// cells may end the row, byte by byte).  Periods are split over blockIdx.y in
+// batches while blocks are fewer than the compute units hold.  1001 x 777
+// cells x 24 periods took 129 us with one block per 2048 cells and period,
+// byte loads and ballots; 15.6 us here; 2048^2 x 48 took 50.0 us with a DPP sum and LDS atomics for
+// each period, 44.4 us with eight periods summed together (4.9 TB/s).
 constexpr int kRowsBlock = 1024;
-constexpr int kRowsMaxPeriods = 4096;
+constexpr int kRowsPeriods = 1024;   // a block's periods at most, 20 bytes of LDS each
+// kRowsMaxBlocks blocks of 16384 cells a stride reach 2^31 - 2 cells in 64
+// strides, 2^20 cells a block.
+constexpr int64_t kRowsMaxBlocks = 2048;
+constexpr int64_t kRowsFill = 256;   // blocks that fill the compute units
 constexpr int kRowsBatch = 8;
 constexpr int kRowsWindow = 127;
 
+// Bit 7 of each byte: is the byte nonzero (other bits have no meaning)?
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) {
-    return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
+    return ((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w;
 }
 
-// Every lane of each 16-lane row ends with the row's sum: exchanges with
-// lane ^ 1 and lane ^ 2 (quad permutations), then the other quad of the
-// half row (half mirror), then the other half (mirror).
-__device__ __forceinline__ uint32_t row_sum16(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);    // quad_perm 1,0,3,2
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);    // quad_perm 2,3,0,1
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);   // row_half_mirror
-    v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);   // row_mirror
-    return v;
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
+}
+// v of lane ^ 1, ^ 2, ^ 4 and ^ 8 (half mirror is ^ 7 and mirror ^ 15 in a row of 16)
+__device__ __forceinline__ uint32_t xor1(uint32_t v) { return dpp<0xB1>(v); }
+__device__ __forceinline__ uint32_t xor2(uint32_t v) { return dpp<0x4E>(v); }
+__device__ __forceinline__ uint32_t xor4(uint32_t v) { return dpp<0x141>(dpp<0x1B>(v)); }
+__device__ __forceinline__ uint32_t xor8(uint32_t v) { return dpp<0x140>(dpp<0x141>(v)); }
+
+// Sums of eight values over each row of 16 lanes, value (lane & 7) in every
+// lane: in three steps each lane keeps the half of its values whose number
+// has its own lane bit, and adds its partner's part of them.
+__device__ __forceinline__ uint32_t row_sums8(const uint32_t* r) {
+    const int lane = (int)__lane_id();
+    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0, b2 = (lane & 4) != 0;
+    uint32_t s[4], u[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = (b0 ? r[2 * k + 1] : r[2 * k]) + xor1(b0 ? r[2 * k] : r[2 * k + 1]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) u[k] = (b1 ? s[2 * k + 1] : s[2 * k]) + xor2(b1 ? s[2 * k] : s[2 * k + 1]);
+    uint32_t v = (b2 ? u[1] : u[0]) + xor4(b2 ? u[0] : u[1]);
+    return v + xor8(v);
 }
 
-template <int CPL>
+// The bits 7 of the bytes of four words, side by side in the high halves of
+// the bytes of one.
+__device__ __forceinline__ uint32_t top_bits(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    const uint32_t ab = (a & 0x80808080u) | (b >> 1 & ~0x80808080u), cd = (c & 0x80808080u) | (d >> 1 & ~0x80808080u);
+    return ((ab & 0xC0C0C0C0u) | (cd >> 2 & ~0xC0C0C0C0u)) & 0xF0F0F0F0u;
+}
+
+// Adds a row's packed sum to a period's count in LDS.
+__device__ __forceinline__ void add_row(unsigned long long* cnt, uint32_t r) {
+    atomicAdd(cnt, (unsigned long long)(r & 1023u) | (unsigned long long)((r >> 10) & 1023u) << 21 |
+                       (unsigned long long)(r >> 20) << 42);
+}
+
+template <bool ALIGNED>
 __global__ __launch_bounds__(kRowsBlock) void scar_counts_rows_kernel(const int32_t* __restrict__ arrival,
                                                                       const uint8_t* __restrict__ reference,
-                                                                      int64_t q, int T, int period_min,
+                                                                      int64_t n, int T, int per_block, int period_min,
                                                                       unsigned long long* __restrict__ counts,
                                                                       uint32_t* __restrict__ ticket,
                                                                       double* __restrict__ out) {
-    constexpr int W = CPL / 4;   // reference words per lane and period
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    extern __shared__ uint32_t s_cnt[];   // [3 T]
-    for (int k = (int)threadIdx.x; k < 3 * T; k += kRowsBlock) s_cnt[k] = 0;
+    typedef u32x4 u32x4_u1 __attribute__((aligned(1)));
+    typedef int32_t i32x4_u4 __attribute__((ext_vector_type(4), aligned(4)));
+    extern __shared__ unsigned long long s_rows[];   // [periods of the block], then 3 u32 counts of each
+    const int p0 = (int)blockIdx.y * per_block, p1 = min(T, p0 + per_block), np = p1 - p0;
+    for (int k = (int)threadIdx.x; k < np; k += kRowsBlock) s_rows[k] = 0;
     __syncthreads();
+    const int64_t q = (n + 15) / 16;
     for (int64_t jb = (int64_t)blockIdx.x * kRowsBlock; jb < q; jb += (int64_t)gridDim.x * kRowsBlock) {
         const int64_t j = jb + threadIdx.x;
-        const bool act = j < q;
-        int32_t kc[CPL];   // burn period of each of the lane's cells (0x7FFFFFFF = never)
+        const int live = j < q ? (int)min((int64_t)16, n - 16 * j) : 0;   // the lane's cells
+        int32_t kc[16];   // burn period of each of the lane's cells (0x7FFFFFFF = never)
 #pragma unroll
-        for (int v = 0; v < W; ++v) {
-            const int4 m = act ? ((const int4*)arrival)[j * W + v] : make_int4(-1, -1, -1, -1);
-            const int32_t mv[4] = {m.x, m.y, m.z, m.w};
+        for (int v = 0; v < 4; ++v) {
+            int32_t m[4] = {-1, -1, -1, -1};
+            if (live == 16) {
+                if constexpr (ALIGNED) {
+                    const int4 x = ((const int4*)arrival)[j * 4 + v];
+                    m[0] = x.x, m[1] = x.y, m[2] = x.z, m[3] = x.w;
+                } else {
+                    const i32x4_u4 x = *(const i32x4_u4*)(arrival + 16 * j + 4 * v);
+                    m[0] = x.x, m[1] = x.y, m[2] = x.z, m[3] = x.w;
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (4 * v + u < live) m[u] = arrival[16 * j + 4 * v + u];
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                kc[4 * v + u] = mv[u] < 0 ? 0x7FFFFFFF : (mv[u] == 0 ? 0 : (mv[u] - 1) / period_min);
+                kc[4 * v + u] = m[u] < 0 ? 0x7FFFFFFF : (m[u] == 0 ? 0 : (m[u] - 1) / period_min);
         }
-        for (int tw = 0; tw < T; tw += kRowsWindow) {
-            uint32_t kb[W];
+        for (int tw = p0; tw < p1; tw += kRowsWindow) {
+            uint32_t kb[4];
 #pragma unroll
-            for (int v = 0; v < W; ++v) {
+            for (int v = 0; v < 4; ++v) {
                 uint32_t w = 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const int32_t r = kc[4 * v + u] - tw;
-                    w |= (uint32_t)(r < 0 ? 0 : (r > kRowsWindow ? kRowsWindow : r)) << (8 * u);
+                    const int32_t k = kc[4 * v + u];
+                    const int32_t r = k <= tw ? 0 : (k - tw > kRowsWindow ? kRowsWindow : k - tw);
+                    w |= (uint32_t)r << (8 * u);
                 }
                 kb[v] = w;
             }
-            const int tend = min(T, tw + kRowsWindow);
+            const int tend = min(p1, tw + kRowsWindow);
             for (int t0 = tw; t0 < tend; t0 += kRowsBatch) {
-                uint32_t wb[kRowsBatch][W];
+                uint32_t wb[kRowsBatch][4];
 #pragma unroll
                 for (int k = 0; k < kRowsBatch; ++k) {
-                    const bool ld = act && t0 + k < tend;
-                    if constexpr (W == 4) {
-                        u32x4 x = {0u, 0u, 0u, 0u};
-                        if (ld) x = ((const u32x4*)reference)[(int64_t)(t0 + k) * q + j];
-                        wb[k][0] = x.x;
-                        wb[k][1] = x.y;
-                        wb[k][2] = x.z;
-                        wb[k][3] = x.w;
-                    } else {
-                        wb[k][0] = ld ? ((const uint32_t*)reference)[(int64_t)(t0 + k) * q + j] : 0u;
+                    u32x4 x = {0u, 0u, 0u, 0u};
+                    const uint8_t* row = reference + (size_t)(t0 + k) * (size_t)n + 16 * (size_t)j;
+                    if (live == 16 && t0 + k < tend) {
+                        if constexpr (ALIGNED) x = *(const u32x4*)row;
+                        else x = *(const u32x4_u1*)row;
+                    }
+                    wb[k][0] = x.x, wb[k][1] = x.y, wb[k][2] = x.z, wb[k][3] = x.w;
+                    if (live > 0 && live < 16 && t0 + k < tend) {
+#pragma unroll
+                        for (int u = 0; u < 15; ++u)
+                            if (u < live) wb[k][u >> 2] |= (uint32_t)row[u] << (8 * (u & 3));
                     }
                 }
+                uint32_t r[kRowsBatch];
 #pragma unroll
                 for (int k = 0; k < kRowsBatch; ++k) {
-                    const int t = t0 + k;
-                    if (t >= tend) break;
-                    const uint32_t tb = ((uint32_t)(t - tw) * 0x01010101u) | 0x80808080u;
-                    uint32_t ca = 0, cb = 0, cc = 0;
-#pragma unroll
-                    for (int v = 0; v < W; ++v) {
-                        const uint32_t xs = nonzero_bytes(wb[k][v]);
-                        const uint32_t ys = (tb - kb[v]) & 0x80808080u;
-                        ca += (uint32_t)__popc(xs);
-                        cb += (uint32_t)__popc(ys);
-                        cc += (uint32_t)__popc(xs & ys);
-                    }
-                    const uint32_t r = row_sum16(ca | cb << 10 | cc << 20);
-                    uint32_t sa = 0, sb = 0, sc = 0;
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)r, 16 * g);
-                        sa += x & 1023u;
-                        sb += (x >> 10) & 1023u;
-                        sc += x >> 20;
-                    }
-                    if (__lane_id() == 0) {
-                        if (sa) atomicAdd(&s_cnt[3 * t], sa);
-                        if (sb) atomicAdd(&s_cnt[3 * t + 1], sb);
-                        if (sc) atomicAdd(&s_cnt[3 * t + 2], sc);
-                    }
+                    const uint32_t tb = ((uint32_t)(t0 + k - tw) * 0x01010101u) | 0x80808080u;
+                    const uint32_t x = top_bits(nonzero_bytes(wb[k][0]), nonzero_bytes(wb[k][1]),
+                                                nonzero_bytes(wb[k][2]), nonzero_bytes(wb[k][3]));
+                    const uint32_t y = top_bits(tb - kb[0], tb - kb[1], tb - kb[2], tb - kb[3]);
+                    r[k] = (uint32_t)__popc(x) | (uint32_t)__popc(y) << 10 | (uint32_t)__popc(x & y) << 20;
                 }
+                const uint32_t v = row_sums8(r);
+                const int k = (int)(threadIdx.x & 15);
+                if (k < kRowsBatch && t0 + k < tend) add_row(&s_rows[t0 + k - p0], v);
             }
         }
     }
-    finish_block(s_cnt, 0, 3 * T, counts, ticket, T, q * CPL, out);
+    // the block's counts as three words a period for finish_block
+    uint32_t* const s_cnt = (uint32_t*)(s_rows + np);
+    __syncthreads();
+    for (int k = (int)threadIdx.x; k < np; k += kRowsBlock) {
+        const unsigned long long v = s_rows[k];
+        s_cnt[3 * k] = (uint32_t)(v & 0x1FFFFFull);
+        s_cnt[3 * k + 1] = (uint32_t)((v >> 21) & 0x1FFFFFull);
+        s_cnt[3 * k + 2] = (uint32_t)(v >> 42);
+    }
+    finish_block(s_cnt, 3 * p0, 3 * np, counts, ticket, T, n, out);
 }
 
 hipError_t launch_scar_metrics(const int32_t* arrival, const uint8_t* reference, int64_t n, int T, int period_min,
                                unsigned long long* counts, uint32_t* ticket, double* out, hipStream_t s) {
     if (n < 2 || T < 1 || T > 65535) return hipErrorInvalidValue;
-    const int cpl = (n % 16 == 0 && (uintptr_t)reference % 16 == 0) ? 16
-                    : (n % 4 == 0 && (uintptr_t)reference % 4 == 0) ? 4 : 0;
-    if (cpl && T <= kRowsMaxPeriods && (uintptr_t)arrival % 16 == 0) {
-        const int64_t q = n / cpl;
-        const int64_t blocks = std::min<int64_t>((q + kRowsBlock - 1) / kRowsBlock, 2048);
-        if (cpl == 16)
-            scar_counts_rows_kernel<16><<<(unsigned)blocks, kRowsBlock, (size_t)12 * T, s>>>(
-                arrival, reference, q, T, period_min, counts, ticket, out);
-        else
-            scar_counts_rows_kernel<4><<<(unsigned)blocks, kRowsBlock, (size_t)12 * T, s>>>(
-                arrival, reference, q, T, period_min, counts, ticket, out);
-    } else {
-        const int64_t per_block = (int64_t)kMetricBlock * kMetricCellsPerThread;
-        const int64_t gx = (n + per_block - 1) / per_block;
-        if (gx * T > 0xFFFFFFFFll) return hipErrorInvalidValue;   // the ticket counts blocks in 32 bits
-        const dim3 grid((unsigned)gx, (unsigned)T);
-        scar_counts_kernel<<<grid, kMetricBlock, 0, s>>>(arrival, reference, n, T, period_min, counts, ticket, out);
-    }
+    const int64_t q = (n + 15) / 16;
+    const int64_t gx = (q + kRowsBlock - 1) / kRowsBlock;   // blocks over the cells
+    // a block takes every period of its cells (kRowsPeriods at most), unless
+    // that leaves the chip short of blocks: then fewer batches of periods each
+    const int64_t batches = (T + kRowsBatch - 1) / kRowsBatch;
+    const int64_t gy = std::min(batches, std::max<int64_t>(1, kRowsFill / gx));
+    const int per_block = (int)std::min<int64_t>((batches + gy - 1) / gy * kRowsBatch, kRowsPeriods);
+    const dim3 grid((unsigned)std::min(gx, kRowsMaxBlocks), (unsigned)((T + per_block - 1) / per_block));
+    const size_t lds = (size_t)std::min(per_block, T) * 20;
+    if (n % 16 == 0 && (uintptr_t)reference % 16 == 0 && (uintptr_t)arrival % 16 == 0)
+        scar_counts_rows_kernel<true><<<grid, kRowsBlock, lds, s>>>(arrival, reference, n, T, per_block, period_min,
+                                                                    counts, ticket, out);
+    else
+        scar_counts_rows_kernel<false><<<grid, kRowsBlock, lds, s>>>(arrival, reference, n, T, per_block, period_min,
+                                                                     counts, ticket, out);
     return hipGetLastError();
 }
 
