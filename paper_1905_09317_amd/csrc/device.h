@@ -126,63 +126,6 @@ __device__ __forceinline__ R rsi_pure(const CoefR<R>& k, R isi) {
     return k.a * rate_pow(-m_expm1(-k.b * isi), k.c);
 }
 
-// Surface fuel consumption (kg/m^2) of an unmixed fuel from FFMC and BUI
-// (M-1/M-2 mix the C-2 and D-1 values by percent conifer where they are
-// used; they get 0 here).
-template <typename R>
-__device__ R surface_consumption(int f, R ffmc, R bui) {
-    switch (f) {
-        case kC1:
-            return ffmc > (R)84 ? (R)0.75 + (R)0.75 * m_sqrt((R)1 - m_exp((R)-0.23 * (ffmc - (R)84)))
-                                : (R)0.75 - (R)0.75 * m_sqrt((R)1 - m_exp((R)-0.23 * ((R)84 - ffmc)));
-        case kC2:
-        case kM3:
-        case kM4: return (R)5 * ((R)1 - m_exp((R)-0.0115 * bui));
-        case kC3:
-        case kC4: return (R)5 * m_pow((R)1 - m_exp((R)-0.0164 * bui), (R)2.24);
-        case kC5:
-        case kC6: return (R)5 * m_pow((R)1 - m_exp((R)-0.0149 * bui), (R)2.48);
-        case kC7: {
-            const R ffc = ffmc > (R)70 ? (R)2 * ((R)1 - m_exp((R)-0.104 * (ffmc - (R)70))) : (R)0;
-            return ffc + (R)1.5 * ((R)1 - m_exp((R)-0.0201 * bui));
-        }
-        case kD1:
-        case kD2: return (R)1.5 * ((R)1 - m_exp((R)-0.0183 * bui));
-        case kS1: return (R)4 * ((R)1 - m_exp((R)-0.025 * bui)) + (R)4 * ((R)1 - m_exp((R)-0.034 * bui));
-        case kS2: return (R)10 * ((R)1 - m_exp((R)-0.013 * bui)) + (R)6 * ((R)1 - m_exp((R)-0.060 * bui));
-        case kS3: return (R)12 * ((R)1 - m_exp((R)-0.0166 * bui)) + (R)20 * ((R)1 - m_exp((R)-0.0210 * bui));
-        case kO1a:
-        case kO1b: return (R)kGrassFuelLoad;
-        default: return (R)0;
-    }
-}
-
-// Fill one table row from FFMC, BUI, wind speed (km/h) and the azimuth the
-// wind comes from.  The fire heads downwind: WAZ = WD + 180 degrees.
-template <typename R>
-__device__ void weather_row(const CoefR<R>* coef, float ffmc_f, float bui_f, float ws_f, float wd_f,
-                            R* row) {
-    const R ffmc = (R)ffmc_f, bui = (R)bui_f, ws = (R)ws_f, wd = (R)wd_f;
-    const R m = (R)147.2 * ((R)101 - ffmc) / ((R)59.5 + ffmc);   // fine fuel moisture
-    const R ff = (R)91.9 * m_exp((R)-0.1386 * m) * ((R)1 + m_pow(m, (R)5.31) / (R)4.93e7);
-    const R isz = (R)0.208 * ff;
-    const R waz = m_fmod(wd + (R)180, (R)360) * (Const<R>::pi / (R)180);
-    row[0] = ff;
-    row[1] = isz;
-    row[2] = ws * m_sin(waz);
-    row[3] = ws * m_cos(waz);
-    for (int f = 0; f < kNumFuels; ++f) {
-        const CoefR<R>& k = coef[f];
-        R be = (R)1;
-        if (f != kNonFuel && bui > (R)0)
-            be = m_exp((R)50 * m_log(k.q) * ((R)1 / bui - (R)1 / k.bui0));
-        row[kRowBE + f] = be;
-        row[kRowG + f] = (k.a > (R)0) ? -m_expm1(-k.b * isz) : (R)0;
-        row[kRowSFC + f] = surface_consumption<R>(f, ffmc, bui);
-    }
-    for (int k = kRowSFC + kNumFuels; k < kRowLen; ++k) row[k] = (R)0;
-}
-
 // ----------------------------------------------------------- cell rates
 __device__ __forceinline__ int rec_fuel(uint32_t info) { return (int)(info & 0xFFu); }
 __device__ __forceinline__ uint32_t rec_nbmask(uint32_t info) { return (info >> 8) & 0xFFu; }
