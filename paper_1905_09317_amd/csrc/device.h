@@ -953,25 +953,6 @@ __device__ __forceinline__ int32_t quantise(R x, R u) {
     return (v < (R)1073741824) ? (int32_t)v : 1073741824;
 }
 
-// axis_q_direct of a quad's cell: qa and qb are the integer rates of axes
-// `role` and `role` + 4.
-template <typename R>
-__device__ __forceinline__ bool quad_axis_q_direct(const EvalLds<R>& x, const EvalLds<double>& x64, const EvalRep& e,
-                                                   const CellRec& rec, const QuadWords& w, int role, int32_t& qa,
-                                                   int32_t& qb) {
-    const CellRates<R> cr = quad_cell_rates<R, MathOf<R>>(x, x64, rec, role);
-    const R mu = e.sigma == 0.f ? (R)1 : noise_of<R, MathOf<R>>(w.n1, w.n2, (R)e.sigma);
-    R xa, xb;
-    quad_axis_rates<R, MathOf<R>>(cr, mu, role, xa, xb);
-    qa = quantise<R>(xa, e.rounding != 0 ? unit24<R>(w.wa) : (R)0.5);
-    qb = quantise<R>(xb, e.rounding != 0 ? unit24<R>(w.wb) : (R)0.5);
-    if (e.hfi_min > 0.f) {
-        const R hfi = head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (R*)nullptr) * mu;
-        return !((double)hfi >= (double)e.hfi_min);
-    }
-    return false;
-}
-
 // The FP64 evaluation of a quad whose FP32 one lies near a rounding boundary:
 // about 0.1 % of evaluations, kept out of line as slope_wind_rare is.
 struct QuadRates {
@@ -987,8 +968,18 @@ static inline __device__ __attribute__((noinline)) QuadRates quad_axis_q_rare(co
     rec.ux = rec.uy = 0.f;   // the FP64 evaluation forms its own
     rec.sfc = sfc;
     rec.sfd = sfd;
+    const CellRates<double> cr = quad_cell_rates<double, MathOf<double>>(*x, *x, rec, role);
+    const double mu = e->sigma == 0.f ? 1.0 : noise_of<double, MathOf<double>>(w.n1, w.n2, (double)e->sigma);
+    double xa, xb;
+    quad_axis_rates<double, MathOf<double>>(cr, mu, role, xa, xb);
     QuadRates o;
-    o.faint = quad_axis_q_direct<double>(*x, *x, *e, rec, w, role, o.qa, o.qb) ? 1u : 0u;
+    o.qa = quantise<double>(xa, e->rounding != 0 ? unit24<double>(w.wa) : 0.5);
+    o.qb = quantise<double>(xb, e->rounding != 0 ? unit24<double>(w.wb) : 0.5);
+    o.faint = 0u;
+    if (e->hfi_min > 0.f) {
+        const double hfi = head_intensity(cr, rec_fuel(rec.info), x->row, x->L, (double*)nullptr) * mu;
+        o.faint = hfi >= (double)e->hfi_min ? 0u : 1u;
+    }
     return o;
 }
 
@@ -1005,19 +996,43 @@ __device__ __forceinline__ int32_t quantise_mixed(float x, float u, bool& exact)
     return (int32_t)k;
 }
 
+// The random part of a quad's evaluation: its words, and in FP32 the noise
+// multiplier.  It needs nothing of the cell's record, so the caller forms it
+// while the record is on its way.
+struct QuadDraws {
+    QuadWords w;
+    float mu;
+};
+template <bool MIXED>
+__device__ __forceinline__ QuadDraws quad_draws(const EvalRep& e, uint32_t cell, uint32_t period, int role) {
+    using M = typename std::conditional<MIXED, MathFast, MathOf<float>>::type;
+    QuadDraws d{{0u, 0u, 0u, 0u}, 1.f};
+    if (e.sigma != 0.f || e.rounding != 0) d.w = quad_words(e.seed, cell, period, e.rep, role);
+    if (e.sigma != 0.f) d.mu = noise_of<float, M>(d.w.n1, d.w.n2, e.sigma);
+    return d;
+}
+
 // axis_q of a quad's cell: FP32 rates (MIXED false), or the integer rates of
 // an FP64 evaluation.
 template <bool MIXED>
 __device__ __forceinline__ bool quad_axis_q(const EvalLds<float>& x, const EvalLds<double>& x64, const EvalRep& e,
-                                            const EvalRep* e_lds, const CellRec& rec, uint32_t cell, uint32_t period,
-                                            int role, int32_t& qa, int32_t& qb) {
-    QuadWords w{0u, 0u, 0u, 0u};
-    if (e.sigma != 0.f || e.rounding != 0) w = quad_words(e.seed, cell, period, e.rep, role);
+                                            const EvalRep* e_lds, const CellRec& rec, const QuadDraws& d, int role,
+                                            int32_t& qa, int32_t& qb) {
+    const QuadWords w = d.w;
+    const float mu = d.mu;
     if constexpr (!MIXED) {
-        return quad_axis_q_direct<float>(x, x64, e, rec, w, role, qa, qb);
+        const CellRates<float> cr = quad_cell_rates<float, MathOf<float>>(x, x64, rec, role);
+        float xa, xb;
+        quad_axis_rates<float, MathOf<float>>(cr, mu, role, xa, xb);
+        qa = quantise<float>(xa, e.rounding != 0 ? unit24<float>(w.wa) : 0.5f);
+        qb = quantise<float>(xb, e.rounding != 0 ? unit24<float>(w.wb) : 0.5f);
+        if (e.hfi_min > 0.f) {
+            const float hfi = head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr) * mu;
+            return !((double)hfi >= (double)e.hfi_min);
+        }
+        return false;
     } else {
         const CellRates<float> cr = quad_cell_rates<float, MathFast>(x, x64, rec, role);
-        const float mu = e.sigma == 0.f ? 1.f : noise_of<float, MathFast>(w.n1, w.n2, e.sigma);
         float xa, xb;
         quad_axis_rates<float, MathFast>(cr, mu, role, xa, xb);
         bool exact = !cr.edge;
@@ -1147,11 +1162,10 @@ __device__ __forceinline__ void lane_axis_rates(const CellRates<float>& cr, floa
     }
 }
 
-// axis_q of one cell a lane, called by the whole wave together.  done = false:
-// the cell needs a quad and the rates have no meaning.
+// The random part of one cell a lane: the noise multiplier and the eight
+// rounding words (1/2 as a 24-bit fraction without stochastic rounding).
 template <bool MIXED>
-__device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalRep& e, const CellRec& rec,
-                                            uint32_t cell, uint32_t period, int32_t* q, bool& done) {
+__device__ __forceinline__ float lane_draws(const EvalRep& e, uint32_t cell, uint32_t period, uint32_t* w) {
     using M = typename std::conditional<MIXED, MathFast, MathOf<float>>::type;
     uint32_t k0 = (uint32_t)e.seed, k1 = (uint32_t)(e.seed >> 32);
     asm volatile("" : "+s"(k0), "+s"(k1));   // as in quad_words
@@ -1160,6 +1174,23 @@ __device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalR
         const uint4 n = philox4x32_10(make_uint4(cell, period, e.rep, 0u), k0, k1);
         mu = noise_of<float, M>(n.x, n.y, e.sigma);
     }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w[k] = 0x80000000u;
+    if (e.rounding != 0) {
+        const uint4 ua = philox4x32_10(make_uint4(cell, period, e.rep, 1u), k0, k1);
+        const uint4 ub = philox4x32_10(make_uint4(cell, period, e.rep, 2u), k0, k1);
+        w[0] = ua.x, w[1] = ua.y, w[2] = ua.z, w[3] = ua.w;
+        w[4] = ub.x, w[5] = ub.y, w[6] = ub.z, w[7] = ub.w;
+    }
+    return mu;
+}
+
+// axis_q of one cell a lane, called by the whole wave together.  done = false:
+// the cell needs a quad and the rates have no meaning.
+template <bool MIXED>
+__device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalRep& e, const CellRec& rec, float mu,
+                                            const uint32_t* w, int32_t* q, bool& done) {
+    using M = typename std::conditional<MIXED, MathFast, MathOf<float>>::type;
     const CellRates<float> cr = lane_cell_rates<M>(x, rec, done);
     if constexpr (MIXED) done = done && !cr.edge;
     bool faint = false;
@@ -1171,15 +1202,6 @@ __device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalR
     }
     float x8[8];
     lane_axis_rates<M>(cr, mu, x8);
-    uint32_t w[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = 0x80000000u;   // 1/2 as a 24-bit fraction
-    if (e.rounding != 0) {
-        const uint4 ua = philox4x32_10(make_uint4(cell, period, e.rep, 1u), k0, k1);
-        const uint4 ub = philox4x32_10(make_uint4(cell, period, e.rep, 2u), k0, k1);
-        w[0] = ua.x, w[1] = ua.y, w[2] = ua.z, w[3] = ua.w;
-        w[4] = ub.x, w[5] = ub.y, w[6] = ub.z, w[7] = ub.w;
-    }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const float u = unit24<float>(w[k]);

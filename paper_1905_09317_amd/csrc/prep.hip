@@ -474,7 +474,9 @@ __global__ __launch_bounds__(256) void eval_q8_kernel(EvalArgs a) {
         const CellRec rec = a.cells[i];
         int32_t qa = 0, qb = 0;
         if (rec_fuel(rec.info) != 0)
-            quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, e, &s_e, rec, (uint32_t)i, (uint32_t)a.period, role, qa, qb);
+            quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, e, &s_e, rec,
+                                        quad_draws<sizeof(R) == 8>(e, (uint32_t)i, (uint32_t)a.period, role), role, qa,
+                                        qb);
         a.q8[(size_t)i * 8 + role] = qa;
         a.q8[(size_t)i * 8 + role + 4] = qb;
     }

@@ -50,7 +50,9 @@
 // a pass at 40 cells on average, 256 registers, 8 waves a compute unit), in ms:
 // 8192^2 x 64 replications x 72 periods 7.70 -> 4.50, 1024^2 x 2048 x 48
 // 39.1 -> 19.6, one FP32 fire on 2048^2 x 48 3.61 -> 2.23, 20 x 20 cells x 10
-// 0.24 -> 0.13.
+// 0.24 -> 0.13.  Drawing the random part (three Philox blocks, the noise)
+// between a pass's loads and their first use, and loading in every lane: 6.91 ->
+// 6.25 and 13.8 -> 12.9 on other weather of the first two.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -539,23 +541,22 @@ __global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restri
                         }
                     }
                     const int off[4] = {1, 1 - cols, -cols, -cols - 1};
-                    CellRec rec;
-                    rec.info = rec.grad = 0u;
-                    rec.ux = rec.uy = 0.f;
-                    rec.sfc = rec.sfd = 1.0;
+                    // every lane loads (an empty one cell 0): a branch here
+                    // would copy the loads' registers behind it and wait
+                    const uint32_t own = load_label(&plane[c]);
+                    const CellRec rec = load_rec(cells + c);
                     uint32_t v[8];
-                    uint32_t own = 0;
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) v[k] = 0u;
-                    if (act) {
-                        own = load_label(&plane[c]);
-                        rec = load_rec(cells + c);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            v[k] = plane[min(c + (uint32_t)off[k], last_cell)];
-                            v[k + 4] = plane[min(c - (uint32_t)off[k], last_cell)];
-                        }
+                    for (int k = 0; k < 4; ++k) {
+                        v[k] = plane[min(c + (uint32_t)off[k], last_cell)];
+                        v[k + 4] = plane[min(c - (uint32_t)off[k], last_cell)];
                     }
+                    // the random part while the loads are on their way (the
+                    // empty asm keeps it there: it would sink to its use)
+                    uint32_t w[8];
+                    float mu = lane_draws<sizeof(R) == 8>(erep, c, (uint32_t)p, w);
+                    asm volatile("" : "+v"(mu), "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]),
+                                 "+v"(w[6]), "+v"(w[7]));
                     act = act && own == lab;
                     const int32_t m0 = max((int32_t)(lab & kMinuteMask) + 1, s);
                     const uint32_t nb = act ? rec_nbmask(rec.info) : 0u;
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restri
                     if (__any(want)) {
                         int32_t q[8];
                         bool done;
-                        bool out = lane_axis_q<sizeof(R) == 8>(s_x32, erep, rec, c, (uint32_t)p, q, done);
+                        bool out = lane_axis_q<sizeof(R) == 8>(s_x32, erep, rec, mu, w, q, done);
                         redo = __ballot(want && !done);
                         if (want && !done) rem[0] = rem[1] = rem[2] = rem[3] = 0u;
                         if (want && done) {
@@ -701,17 +702,15 @@ __global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restri
                     // and clamps too) and never used: the record's neighbour mask
                     // (in-grid burnable cells) excludes its axis.  Grids hold
                     // fewer than 2^31 cells.
-                    CellRec rec;
-                    rec.info = 0;
-                    uint32_t vA = 0, vB = 0;
                     const uint32_t cA = c + (uint32_t)offk, cB = c - (uint32_t)offk;
-                    if (act) {
-                        const uint32_t own = load_label(&plane[c]);
-                        rec = load_rec(cells + c);
-                        vA = plane[min(cA, last_cell)];
-                        vB = plane[min(cB, last_cell)];
-                        act = own == lab;
-                    }
+                    const uint32_t own = load_label(&plane[c]);
+                    const CellRec rec = load_rec(cells + c);
+                    const uint32_t vA = plane[min(cA, last_cell)], vB = plane[min(cB, last_cell)];
+                    // the random part while the loads are on their way
+                    // (the empty asm keeps it there: it would sink to its use)
+                    QuadDraws draws = quad_draws<sizeof(R) == 8>(erep, c, (uint32_t)p, role);
+                    asm volatile("" : "+v"(draws.mu), "+v"(draws.w.n1), "+v"(draws.w.n2), "+v"(draws.w.wa), "+v"(draws.w.wb));
+                    act = act && own == lab;
 
                     int32_t candA = kNever, candB = kNever;
                     bool keep = false;
@@ -726,7 +725,7 @@ __global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restri
                         if (!(nb & 16u) || !axis_live(remB, dB, m0)) remB = 0;
                         if (quad_or((uint32_t)(remA | remB)) != 0u && m0 <= e) {
                             int32_t qA, qB;
-                            bool out = quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, erep, &s_e, rec, c, (uint32_t)p, role, qA, qB);
+                            bool out = quad_axis_q<sizeof(R) == 8>(s_x32, s_x64, erep, &s_e, rec, draws, role, qA, qB);
                             c_evals += role == 0;
                             // burn-out (A5 (iv)): the head fire intensity is below
                             // the threshold; (A5 (i)): every rate toward a burnable
