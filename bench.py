@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("b1daa1667f81c070", 10_922_645),
-    "batched-mc-1024x1024-2048reps": ("b1daa1667f81c070", 45_124_195_530),
-    "large-8192x8192-64reps-72h": ("b1daa1667f81c070", 810_805_781),
+    "single-fire-2048x2048-48h": ("90bac853c02a41c5", 10_904_853),
+    "batched-mc-1024x1024-2048reps": ("90bac853c02a41c5", 45_069_626_784),
+    "large-8192x8192-64reps-72h": ("90bac853c02a41c5", 811_397_632),
 }
 
 

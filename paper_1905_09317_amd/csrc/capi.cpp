@@ -724,23 +724,30 @@ LaunchPlan plan_launch(c2f_ctx* ctx, int64_t cells, int32_t total_items, int32_t
             // replication has a compute unit, or nearly one, to itself.  More
             // replications than that are better served by two groups of 512
             // threads a unit, and many small grids, whose periods hold few
-            // cells, by four of 256.  Kernel times in ms at 1024 / 512 / 256
-            // threads, FP64 results, 48 periods (64^2: 24):
-            //   1024^2   256 replications   4.88 /  5.67 /  8.46
-            //   1024^2   768                7.44 /  6.45 /  9.14
-            //    512^2   512                5.32 /  5.58 /  7.46
-            //    512^2  2048               14.9  / 10.5  / 10.6
-            //    256^2   512                4.13 /  3.78 /  5.22
-            //    256^2  2048               11.5  /  7.90 /  7.21
-            //     64^2   512                1.22 /  0.90 /  0.96
-            //     64^2  2048                3.68 /  2.22 /  1.51
+            // cells, by five of 256.  Kernel times in ms at 1024 / 512 / 256
+            // threads, FP64 results, 48 periods (64^2 and 128^2: 24):
+            //   1024^2   256 replications   4.52 /  5.14 /  7.80
+            //   1024^2   768                6.79 /  5.92 /  8.09
+            //    512^2   512                4.85 /  5.10 /  6.71
+            //    512^2   768                6.12 /  5.16 /  7.34
+            //    512^2  2048               13.5  /  9.80 /  9.59
+            //    256^2   512                3.73 /  3.53 /  4.63
+            //    256^2  1280                7.07 /  5.26 /  5.37
+            //    256^2  2048               10.5  /  7.17 /  6.45
+            //    128^2  1280                2.80 /  1.79 /  1.50
+            //     64^2   512                1.12 /  0.84 /  0.88
+            //     64^2  2048                3.38 /  2.02 /  1.32
+            // and with other ignitions, at 512 / 256 threads:
+            //   1024^2  1536                        6.94 /  7.09
+            //    512^2  1536                        6.39 /  6.24
+            //    512^2  4800                       16.3  / 13.5
             // FP64 results on large grids keep 512-thread groups.
             const int64_t n_cu = ctx->n_cu, items = total_items;
             if (precision == 0 && items <= n_cu && cells >= (1 << 20))
                 lp.block = 512;
             else if (items <= n_cu || (items <= 2 * n_cu && cells >= (1 << 18)))
                 lp.block = 1024;
-            else if (items > 4 * n_cu && cells <= (1 << 16))
+            else if ((items > 4 * n_cu && cells <= (1 << 14)) || (items > 5 * n_cu && cells <= (1 << 18)))
                 lp.block = 256;
             else
                 lp.block = 512;

@@ -158,14 +158,19 @@ __device__ __forceinline__ bool axis_live(int32_t rem, uint32_t d, int32_t m0) {
     return rem > 0 && d > (uint32_t)m0 && d != kPendingMinute;
 }
 
-// 4 waves per SIMD (128 VGPRs; 107 are used).  With narrow passes alone, 5, 6
-// and 8 waves spilled 80, 144 and 208 bytes per lane and were 4, 22 and 60 %
-// slower on 8192^2 x 64 replications x 72 periods at 1024 threads.
+// 93 VGPRs are used, so 5 waves a SIMD would fit; groups of 256 threads are the
+// ones whose LDS then takes five a compute unit (queues of 2048 entries), and
+// are built for it, wider ones for 4.  At 5 against 4 groups of 256 a unit:
+// 64^2 x 5000 replications x 24 periods 2.49 against 2.82 ms, 256^2 x 4800 x 48
+// 9.47 against 10.44, 512^2 x 4800 x 48 13.5 against 14.7; at five replications
+// a unit and fewer it is no faster (128^2 x 1280 x 24: 1.50 against 1.41).
+// (With narrow passes alone, 6 and 8 waves spilled 144 and 208 bytes a lane and
+// were 22 and 60 % slower at 1024 threads.)
 template <typename R, int BLOCK>
-__global__ __launch_bounds__(BLOCK, 4) void propagate_kernel(const Job* __restrict__ jobs, int n_jobs,
+__global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(const Job* __restrict__ jobs, int n_jobs,
                                                           int total_items, Slots slots,
                                                           RunCounters* __restrict__ rc) {
-    constexpr int LQ = BLOCK <= 64 ? 1024 : (BLOCK <= 128 ? 2048 : 4096);   // LDS part of the period queue
+    constexpr int LQ = BLOCK <= 64 ? 1024 : (BLOCK <= 256 ? 2048 : 4096);   // LDS part of the period queue
     __shared__ uint2 s_Q[LQ];
     __shared__ int s_res, s_commit;   // queue entries reserved, committed (in order)
     // queue entries taken (high 32 bits) and waves holding a chunk (low 32),
