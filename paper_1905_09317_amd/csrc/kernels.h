@@ -31,8 +31,9 @@ hipError_t launch_fbp_consts(LandDev* land, float fmc, float pdf, hipStream_t s)
 hipError_t launch_scar_metrics(const int32_t* arrival, const uint8_t* reference, int64_t n, int T, int period_min,
                                unsigned long long* counts, uint32_t* ticket, double* out, hipStream_t s);
 
-// fuel[cells[k]] = codes[k] for k < n.
-hipError_t launch_fuel_edits(uint8_t* fuel, const int32_t* cells, const uint8_t* codes, int64_t n, hipStream_t s);
+// fuel[cells[k]] = codes[k] for k < n in the order of k; owner: scratch, one word a cell.
+hipError_t launch_fuel_edits(uint8_t* fuel, int32_t* owner, const int32_t* cells, const uint8_t* codes, int32_t n,
+                             hipStream_t s);
 int64_t tile_scratch_entries(int64_t n_cells);
 
 // Per (scenario, period) weather terms in FP64 and FP32; wx is [n_rows][4].
