@@ -49,6 +49,28 @@ def test_rule_for_many_replications(sim, shape, more, block, precision):
         sim.unset_weather(w)
 
 
+@pytest.mark.parametrize("shape,precision,block", [((64, 64), 0, 512), ((300, 200), 0, 1024), ((512, 513), 1, 1024),
+                                                   ((1024, 1025), 0, 1024)])
+def test_groups_held_back_by_scratch_are_wide(sim, shape, precision, block):
+    fuel, elev, wx = _landscape(*shape, seed=shape[1])
+    reps = 6 * torch.cuda.get_device_properties(0).multi_processor_count
+    kw = dict(n_periods=3, reps=reps, seed=8, sigma=0.1, rounding=1, precision=precision, ignition_mode=1,
+              scenario_mode=1, outputs=("burn_count", "burned_cells", "ignition_cell"), device_out=True)
+    print(f"held back: {shape}, {reps}, precision {precision}", flush=True)
+    land, w = sim.load_landscape(fuel, elev), sim.set_weather(wx, period_min=60)
+    try:
+        a = sim.simulate_noalloc(Request(landscape=land, weather=w, **kw))
+        st = sim.stats()
+        assert st["grid_blocks"] < reps and st["block_threads"] == block
+        b = sim.simulate(Request(landscape=land, weather=w, **kw))
+        torch.cuda.synchronize()
+        for k in kw["outputs"]:
+            assert torch.equal(a[k].cpu(), b[k].cpu()), k
+    finally:
+        sim.unload_landscape(land)
+        sim.unset_weather(w)
+
+
 def test_frontier_wider_than_the_queue(sim):
     fuel = np.full((96, 96), 15, np.uint8)
     wx = np.tile(np.float32([96, 120, 30, 45]), (1, 4, 1))
