@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("90bac853c02a41c5", 10_904_853),
-    "batched-mc-1024x1024-2048reps": ("90bac853c02a41c5", 45_069_626_784),
-    "large-8192x8192-64reps-72h": ("90bac853c02a41c5", 811_397_632),
+    "single-fire-2048x2048-48h": ("4cf7cc2b332ac021", 10_860_554),
+    "batched-mc-1024x1024-2048reps": ("4cf7cc2b332ac021", 45_109_160_459),
+    "large-8192x8192-64reps-72h": ("4cf7cc2b332ac021", 811_250_005),
 }
 
 

@@ -187,7 +187,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
     // later step: s_refill (the slot's plane needs refilling) and s_stop
     // (leave the period loop after this period).
     __shared__ int s_refill, s_stop;
-    __shared__ unsigned long long s_cnt[kNumCounters];
+    // of the replication, and of all the group has run: its replications' sums
+    // go to the launch's counters together.  Nine device atomics a replication,
+    // all on one line, were most of a launch of many short fires: 5000 fires of
+    // 20^2 that hardly spread took 0.77 ms, 0.15 with the sums; 300 took 57 and
+    // 34 us.
+    __shared__ unsigned long long s_cnt[kNumCounters], s_sum[kNumCounters];
     // what the evaluations read: the curves, the weather rows of the period
     // being propagated (staged at the start of each period) and the
     // landscape's constants, in both precisions
@@ -201,6 +206,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int quad = (tid & 63) >> 2, role = tid & 3;   // the lane's cell of a chunk, its axes there
     __builtin_amdgcn_s_setprio(1);
+    if (tid < kNumCounters) s_sum[tid] = 0;
     if (tid < kNumCurves) {
         s_x64.coef[tid] = curve_entry<double>(tid);
         s_x32.coef[tid] = curve_entry<float>(tid);
@@ -874,10 +880,13 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
             if (job.burned) job.burned[lr] = (int64_t)s_cnt[kCntIgnitions];
             if (job.ign_out) job.ign_out[lr] = s_ign;
             if (job.scen_out) job.scen_out[lr] = s_scen;
-            for (int k = 0; k < kCntMaxList; ++k) atomicAdd(&rc->c[k], s_cnt[k]);
-            atomicMax(&rc->c[kCntMaxList], s_cnt[kCntMaxList]);
         }
+        if (tid < kNumCounters) s_sum[tid] = tid == kCntMaxList ? max(s_sum[tid], s_cnt[tid]) : s_sum[tid] + s_cnt[tid];
         __syncthreads();
+    }
+    if (tid < kNumCounters && s_sum[tid] != 0) {   // each by the thread that summed it
+        if (tid == kCntMaxList) atomicMax(&rc->c[tid], s_sum[tid]);
+        else atomicAdd(&rc->c[tid], s_sum[tid]);
     }
 }
 

@@ -71,6 +71,23 @@ def test_groups_held_back_by_scratch_are_wide(sim, shape, precision, block):
         sim.unset_weather(w)
 
 
+@pytest.mark.parametrize("reps", [1, 256, 3000])
+def test_launch_counters_sum_the_replications(sim, reps):
+    fuel, elev, wx = _landscape(9, 8, seed=2)
+    kw = dict(n_periods=4, reps=reps, seed=6, sigma=0.1, ignition_mode=1, scenario_mode=1)
+    print(f"counters: {reps}", flush=True)
+    land, w = sim.load_landscape(fuel, elev), sim.set_weather(wx, period_min=60)
+    try:
+        for _ in range(2):   # nothing is carried into the next launch
+            r = sim.simulate(Request(landscape=land, weather=w, **kw))
+            st = sim.stats()
+            assert st["ignitions"] == int(np.asarray(r["burned_cells"]).sum())
+            assert st["entries"] >= st["ignitions"] > 0 and st["continuations"] > 0 and st["rate_evals"] > 0
+    finally:
+        sim.unload_landscape(land)
+        sim.unset_weather(w)
+
+
 def test_frontier_wider_than_the_queue(sim):
     fuel = np.full((96, 96), 15, np.uint8)
     wx = np.tile(np.float32([96, 120, 30, 45]), (1, 4, 1))
