@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("4cf7cc2b332ac021", 10_860_554),
-    "batched-mc-1024x1024-2048reps": ("4cf7cc2b332ac021", 45_109_160_459),
-    "large-8192x8192-64reps-72h": ("4cf7cc2b332ac021", 811_250_005),
+    "single-fire-2048x2048-48h": ("b51dad54ada9f231", 10_906_389),
+    "batched-mc-1024x1024-2048reps": ("b51dad54ada9f231", 45_087_348_522),
+    "large-8192x8192-64reps-72h": ("b51dad54ada9f231", 810_350_869),
 }
 
 

@@ -158,7 +158,7 @@ __device__ __forceinline__ bool axis_live(int32_t rem, uint32_t d, int32_t m0) {
     return rem > 0 && d > (uint32_t)m0 && d != kPendingMinute;
 }
 
-// 93 VGPRs are used, so 5 waves a SIMD would fit; groups of 256 threads are the
+// Up to 95 VGPRs are used, so 5 waves a SIMD would fit; groups of 256 threads are the
 // ones whose LDS then takes five a compute unit (queues of 2048 entries), and
 // are built for it, wider ones for 4.  At 5 against 4 groups of 256 a unit:
 // 64^2 x 5000 replications x 24 periods 2.49 against 2.82 ms, 256^2 x 4800 x 48
