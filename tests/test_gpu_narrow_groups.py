@@ -71,6 +71,25 @@ def test_groups_held_back_by_scratch_are_wide(sim, shape, precision, block):
         sim.unset_weather(w)
 
 
+@pytest.mark.parametrize("shape,reps,block", [((1024, 1024), 1, 1024), ((2047, 2048), 1, 1024), ((2048, 2048), 1, 512),
+                                              ((2048, 2049), 2, 1024)])
+def test_width_of_few_fp64_fires(sim, shape, reps, block):
+    fuel, elev, wx = _landscape(*shape, seed=shape[1])
+    kw = dict(n_periods=4, reps=reps, seed=11, sigma=0.1, rounding=1, ignition_mode=1)
+    print(f"few fires: {shape}, {reps}", flush=True)
+    land, w = sim.load_landscape(fuel, elev), sim.set_weather(wx, period_min=60)
+    try:
+        a = sim.simulate(Request(landscape=land, weather=w, **kw))
+        assert sim.stats()["block_threads"] == block
+        sim.set_tuning(1536 - block)   # the other width
+        b = sim.simulate(Request(landscape=land, weather=w, **kw))
+        assert_same_outputs(a, b, where=f"{shape} {reps}")
+    finally:
+        sim.set_tuning(0)
+        sim.unload_landscape(land)
+        sim.unset_weather(w)
+
+
 @pytest.mark.parametrize("reps", [1, 256, 3000])
 def test_launch_counters_sum_the_replications(sim, reps):
     fuel, elev, wx = _landscape(9, 8, seed=2)
