@@ -168,49 +168,126 @@ __global__ void burnable_scatter_kernel(const uint8_t* __restrict__ fuel, int64_
     }
 }
 
-// Burnable cell nearest to (rows/2, cols/2); ties go to the lower index.
-// Blocks take rows outward from the centre row, and a block ends at the first
-// row that lies farther away than the nearest cell found so far, so beyond
-// the rows of the blocks that start together little is read.  A key is d^2 <<
-// 32 | index; a block offers one for a row, and only if it is still smaller:
-// thousands of atomics on the one word were most of the time.  One key of every
-// wave of every 256 cells went through an atomic before: 1500 x 1100 cells 291
-// -> 6.9 us, 8192^2 11755 -> 15.8.
-__global__ __launch_bounds__(256) void centre_kernel(const uint8_t* __restrict__ fuel, int rows, int cols,
-                                                     LandDev* land) {
-    __shared__ unsigned long long s_key[4], s_best;
+// Burnable cell nearest to (rows/2, cols/2); ties go to the lower index.  A
+// squared distance needs up to 62 bits and an index 31, more than one atomic
+// holds, so the least distance is found first and its lowest index after that.
+//
+// Blocks take tiles of kCentreTile consecutive cells outward from the centre
+// cell, before it and behind it in turn, and a block ends at the first tile both
+// of whose sides have only rows as far away as the nearest cell found so far:
+// beyond the tiles of the blocks that start together little is read.  A block
+// offers a distance only if it is still smaller: thousands of atomics on the one
+// word were most of the time.  Bound by the launch and one tile's latency: 1500 x
+// 1100 cells 5.6 us, 8192^2 7.4, 1 x 4 million 9.2, 8192^2 with fuel in one corner
+// only 79 (a key of each wave through an atomic, the whole grid: 291 and 11755
+// for the first two; blocks of whole rows: 6.3, 14.4, 4290 and 309).
+constexpr int kCentreThreads = 256;
+constexpr int kCentreTile = kCentreThreads * 16;
+
+__global__ __launch_bounds__(kCentreThreads) void centre_kernel(const uint8_t* __restrict__ fuel, int rows, int cols,
+                                                                LandDev* land) {
+    __shared__ unsigned long long s_d2[kCentreThreads / 64], s_best;
+    const int64_t n = (int64_t)rows * cols, n_tiles = (n + kCentreTile - 1) / kCentreTile;
     const int cr = rows / 2, cc = cols / 2;
+    const int64_t tc = ((int64_t)cr * cols + cc) / kCentreTile;
     auto nearest = [&]() {
-        return __hip_atomic_load(&land->centre_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return __hip_atomic_load(&land->centre_d2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    for (int64_t o = blockIdx.x; o < 2 * (int64_t)rows; o += gridDim.x) {
-        const int64_t dr = (o & 1) ? -(o + 1) / 2 : o / 2, r = cr + dr;
+    // the least squared row distance of tile tc + m and those behind it, and
+    // of tile tc - 1 - m and those before it
+    auto behind = [&](int64_t m) -> unsigned long long {
+        if (tc + m >= n_tiles) return ~0ull;
+        const int64_t dr = (int64_t)((uint32_t)((tc + m) * kCentreTile) / (uint32_t)cols) - cr;
+        return dr > 0 ? (unsigned long long)(dr * dr) : 0ull;
+    };
+    auto before = [&](int64_t m) -> unsigned long long {
+        if (m >= tc) return ~0ull;
+        const int64_t dr = cr - (int64_t)((uint32_t)((tc - m) * kCentreTile - 1) / (uint32_t)cols);
+        return dr > 0 ? (unsigned long long)(dr * dr) : 0ull;
+    };
+    for (int64_t o = blockIdx.x; o < 2 * n_tiles; o += gridDim.x) {
+        const int64_t m = o >> 1;
         if (threadIdx.x == 0) s_best = nearest();
         __syncthreads();
-        if ((unsigned long long)(dr * dr) > s_best >> 32) break;   // the same for every thread
-        if (r < 0 || r >= rows) {
+        // no cell yet: s_best is above every distance, so that only tiles
+        // outside the grid end the search (the same for every thread)
+        const unsigned long long b0 = behind(m), b1 = before(m), best = s_best;
+        if (b0 >= best && b1 >= best) break;
+        if (((o & 1) ? b1 : b0) >= best) {
             __syncthreads();
             continue;
         }
-        unsigned long long key = ~0ull;
-        for (int c = (int)threadIdx.x; c < cols; c += 256) {
-            if (fuel[r * cols + c] == 0) continue;
-            const int64_t dc = c - cc;
-            const unsigned long long k =
-                ((unsigned long long)(dr * dr + dc * dc) << 32) | (unsigned long long)(r * cols + c);
-            key = k < key ? k : key;
+        const int64_t i0 = ((o & 1) ? tc - 1 - m : tc + m) * kCentreTile + 16 * (int64_t)threadIdx.x;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        if (i0 + 16 <= n) {
+            const uint4 x = *(const uint4*)(fuel + i0);   // the grid starts on a 256-byte boundary
+            w[0] = x.x, w[1] = x.y, w[2] = x.z, w[3] = x.w;
+        } else {
+            for (int u = 0; u < 16; ++u)
+                if (i0 + u < n) w[u >> 2] |= (uint32_t)fuel[i0 + u] << (8 * (u & 3));
+        }
+        unsigned long long d2 = ~0ull;
+        if ((w[0] | w[1] | w[2] | w[3]) != 0u) {
+            const uint32_t r0 = (uint32_t)i0 / (uint32_t)cols;   // indices are below 2^31
+            int64_t dr = (int64_t)r0 - cr, dc = i0 - (int64_t)r0 * cols - cc;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                if ((w[u >> 2] >> (8 * (u & 3))) & 0xFFu) {
+                    const unsigned long long d = (unsigned long long)(dr * dr + dc * dc);
+                    d2 = d < d2 ? d : d2;
+                }
+                if (++dc == cols - cc) dc = -cc, ++dr;
+            }
         }
         for (int off = 32; off > 0; off >>= 1) {
-            const unsigned long long k = __shfl_xor(key, off);
-            key = k < key ? k : key;
+            const unsigned long long d = __shfl_xor(d2, off);
+            d2 = d < d2 ? d : d2;
         }
-        if ((threadIdx.x & 63) == 0) s_key[threadIdx.x >> 6] = key;
+        if ((threadIdx.x & 63) == 0) s_d2[threadIdx.x >> 6] = d2;
         __syncthreads();
         if (threadIdx.x == 0) {
-            for (int w = 1; w < 4; ++w) key = s_key[w] < key ? s_key[w] : key;
-            if (key < nearest()) atomicMin(&land->centre_key, key);
+            for (int k = 1; k < kCentreThreads / 64; ++k) d2 = s_d2[k] < d2 ? s_d2[k] : d2;
+            if (d2 < nearest()) atomicMin(&land->centre_d2, d2);
         }
     }
+}
+
+// Largest r with r r <= x (x < 2^62).
+__device__ __forceinline__ int64_t isqrt(int64_t x) {
+    int64_t r = (int64_t)sqrt((double)x);
+    while (r * r > x) --r;
+    while ((r + 1) * (r + 1) <= x) ++r;
+    return r;
+}
+
+// The lowest index at the least distance.  In a row only the columns at
+// sqrt(d^2 - dr^2) either side of the centre have it, and only the rows whose
+// columns there lie in the grid are looked at.  One block.
+__global__ __launch_bounds__(kCentreThreads) void centre_index_kernel(const uint8_t* __restrict__ fuel, int rows,
+                                                                      int cols, LandDev* land) {
+    __shared__ uint32_t s_cell;
+    if (threadIdx.x == 0) s_cell = 0xFFFFFFFFu;
+    __syncthreads();
+    if (land->centre_d2 != ~0ull) {
+        // cr rows and cc columns lie on the longer sides of the centre cell
+        const int64_t cr = rows / 2, cc = cols / 2, d2 = (int64_t)land->centre_d2;
+        const int64_t near = d2 > cc * cc ? isqrt(d2 - cc * cc) : 0;
+        const int64_t root = isqrt(d2), far = root < cr ? root : cr;
+        auto look = [&](int64_t dr) {
+            const int64_t r = cr + dr, dc2 = d2 - dr * dr;
+            if (r < 0 || r >= rows || dc2 < 0) return;
+            const int64_t dc = isqrt(dc2);
+            if (dc * dc != dc2) return;
+            if (dc <= cc && fuel[r * cols + cc - dc] != 0) atomicMin(&s_cell, (uint32_t)(r * cols + cc - dc));
+            if (cc + dc < cols && fuel[r * cols + cc + dc] != 0) atomicMin(&s_cell, (uint32_t)(r * cols + cc + dc));
+        };
+        for (int64_t k = near + threadIdx.x; k <= far; k += kCentreThreads) {
+            look(-k);
+            look(k);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) land->centre_cell = (int32_t)s_cell;   // -1 if there is none
 }
 
 // Landscape constants: M-1/M-2 conifer fraction and the O-1 curing factor
@@ -252,7 +329,7 @@ __global__ void landinit_kernel(LandDev* land, float pc, float curing, int cell_
     land->n_burnable = 0;
     land->centre_cell = -1;
     land->grad_overflow = land->pad0 = 0;
-    land->centre_key = ~0ull;
+    land->centre_d2 = ~0ull;
     const double c = (double)curing;
     land->pc_w64 = (double)pc / 100.0;
     land->cf64 = (c < 58.8) ? 0.005 * (exp(0.061 * c) - 1.0) : 0.176 + 0.02 * (c - 58.8);
@@ -262,12 +339,6 @@ __global__ void landinit_kernel(LandDev* land, float pc, float curing, int cell_
     land->cf32 = (cf < 58.8f) ? 0.005f * (expf(0.061f * cf) - 1.0f) : 0.176f + 0.02f * (cf - 58.8f);
     land->cell_m32 = (float)cell_m;
     land->pad1 = 0.f;
-}
-
-__global__ void landdone_kernel(LandDev* land) {
-    if (threadIdx.x != 0) return;
-    const unsigned long long key = land->centre_key;
-    land->centre_cell = (key == ~0ull) ? -1 : (int32_t)(key & 0xFFFFFFFFull);
 }
 
 hipError_t launch_prepare_landscape(const uint8_t* fuel, const int16_t* elev, const CellRec* grad_from,
@@ -283,8 +354,10 @@ hipError_t launch_prepare_landscape(const uint8_t* fuel, const int16_t* elev, co
     hipLaunchKernelGGL(burnable_count_kernel, dim3(n_tiles), dim3(kTileThreads), 0, s, fuel, n, tile_scratch);
     hipLaunchKernelGGL(burnable_scan_kernel, dim3(1), dim3(1024), 0, s, tile_scratch, n_tiles, land);
     hipLaunchKernelGGL(burnable_scatter_kernel, dim3(n_tiles), dim3(kTileThreads), 0, s, fuel, n, tile_scratch, burnable);
-    hipLaunchKernelGGL(centre_kernel, dim3(rows < 256 ? rows : 256), dim3(256), 0, s, fuel, rows, cols, land);
-    hipLaunchKernelGGL(landdone_kernel, dim3(1), dim3(64), 0, s, land);
+    const int64_t centre_tiles = 2 * ((n + kCentreTile - 1) / kCentreTile);
+    hipLaunchKernelGGL(centre_kernel, dim3((unsigned)(centre_tiles < 256 ? centre_tiles : 256)), dim3(kCentreThreads),
+                       0, s, fuel, rows, cols, land);
+    hipLaunchKernelGGL(centre_index_kernel, dim3(1), dim3(kCentreThreads), 0, s, fuel, rows, cols, land);
     return hipGetLastError();
 }
 
