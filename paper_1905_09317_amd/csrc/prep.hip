@@ -170,7 +170,8 @@ __global__ void burnable_scatter_kernel(const uint8_t* __restrict__ fuel, int64_
 
 // Burnable cell nearest to (rows/2, cols/2); ties go to the lower index.  A
 // squared distance needs up to 62 bits and an index 31, more than one atomic
-// holds, so the least distance is found first and its lowest index after that.
+// holds, so the least distance (centre_key) is found first and its lowest index
+// after that.
 //
 // Blocks take tiles of kCentreTile consecutive cells outward from the centre
 // cell, before it and behind it in turn, and a block ends at the first tile both
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(kCentreThreads) void centre_kernel(const uint8_t* _
     const int cr = rows / 2, cc = cols / 2;
     const int64_t tc = ((int64_t)cr * cols + cc) / kCentreTile;
     auto nearest = [&]() {
-        return __hip_atomic_load(&land->centre_d2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return __hip_atomic_load(&land->centre_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     // the least squared row distance of tile tc + m and those behind it, and
     // of tile tc - 1 - m and those before it
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(kCentreThreads) void centre_kernel(const uint8_t* _
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int k = 1; k < kCentreThreads / 64; ++k) d2 = s_d2[k] < d2 ? s_d2[k] : d2;
-            if (d2 < nearest()) atomicMin(&land->centre_d2, d2);
+            if (d2 < nearest()) atomicMin(&land->centre_key, d2);
         }
     }
 }
@@ -268,9 +269,9 @@ __global__ __launch_bounds__(kCentreThreads) void centre_index_kernel(const uint
     __shared__ uint32_t s_cell;
     if (threadIdx.x == 0) s_cell = 0xFFFFFFFFu;
     __syncthreads();
-    if (land->centre_d2 != ~0ull) {
+    if (land->centre_key != ~0ull) {
         // cr rows and cc columns lie on the longer sides of the centre cell
-        const int64_t cr = rows / 2, cc = cols / 2, d2 = (int64_t)land->centre_d2;
+        const int64_t cr = rows / 2, cc = cols / 2, d2 = (int64_t)land->centre_key;
         const int64_t near = d2 > cc * cc ? isqrt(d2 - cc * cc) : 0;
         const int64_t root = isqrt(d2), far = root < cr ? root : cr;
         auto look = [&](int64_t dr) {
@@ -329,7 +330,7 @@ __global__ void landinit_kernel(LandDev* land, float pc, float curing, int cell_
     land->n_burnable = 0;
     land->centre_cell = -1;
     land->grad_overflow = land->pad0 = 0;
-    land->centre_d2 = ~0ull;
+    land->centre_key = ~0ull;
     const double c = (double)curing;
     land->pc_w64 = (double)pc / 100.0;
     land->cf64 = (c < 58.8) ? 0.005 * (exp(0.061 * c) - 1.0) : 0.176 + 0.02 * (c - 58.8);

@@ -56,7 +56,7 @@ struct LandDev {
     int32_t centre_cell;       // burnable cell nearest (rows/2, cols/2), -1 if none
     int32_t grad_overflow;     // a Horn numerator left the int16 range
     int32_t pad0;
-    unsigned long long centre_d2;   // its squared distance in cells, ~0 if none
+    unsigned long long centre_key;
     double pc_w64, cf64, cell_m64;
     float pc_w32, cf32, cell_m32, pad1;
     // percent dead fir / 100 (M-3, M-4), and the C-6 foliar moisture effect
