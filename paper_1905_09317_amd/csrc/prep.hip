@@ -462,17 +462,22 @@ __device__ void weather_row(const CoefR<R>* coef, float ffmc_f, float bui_f, flo
 
 // One wave a row, lane f for fuel f; blockIdx.y selects the precision.  (One
 // thread a row took its 19 fuels in turn: 10.4 + 4.8 us for up to 100 rows in
-// two launches, 9 us here.)
-__global__ __launch_bounds__(64) void weather_table_kernel(const float* __restrict__ wx, double* __restrict__ t64,
-                                                           float* __restrict__ t32) {
-    const size_t i = blockIdx.x;
-    const float* w = wx + i * 4;
-    if (blockIdx.y == 0) weather_row<double>(coef_table<double>(), w[0], w[1], w[2], w[3], t64 + i * kRowLen);
-    else weather_row<float>(coef_table<float>(), w[0], w[1], w[2], w[3], t32 + i * kRowLen);
+// two launches, 9 us here.)  A launch holds fewer than 2^32 threads along an
+// axis, and a table up to 2^26 rows, so a wave takes several from 2^20 on.
+constexpr int kWeatherWaves = 1 << 20;
+
+__global__ __launch_bounds__(64) void weather_table_kernel(const float* __restrict__ wx, int n_rows,
+                                                           double* __restrict__ t64, float* __restrict__ t32) {
+    for (size_t i = blockIdx.x; i < (size_t)n_rows; i += gridDim.x) {
+        const float* w = wx + i * 4;
+        if (blockIdx.y == 0) weather_row<double>(coef_table<double>(), w[0], w[1], w[2], w[3], t64 + i * kRowLen);
+        else weather_row<float>(coef_table<float>(), w[0], w[1], w[2], w[3], t32 + i * kRowLen);
+    }
 }
 
 hipError_t launch_weather_table(const float* wx, int n_rows, double* t64, float* t32, hipStream_t s) {
-    hipLaunchKernelGGL(weather_table_kernel, dim3((unsigned)n_rows, 2), dim3(64), 0, s, wx, t64, t32);
+    const unsigned waves = (unsigned)(n_rows < kWeatherWaves ? n_rows : kWeatherWaves);
+    hipLaunchKernelGGL(weather_table_kernel, dim3(waves, 2), dim3(64), 0, s, wx, n_rows, t64, t32);
     return hipGetLastError();
 }
 
