@@ -68,9 +68,12 @@ struct TuneKey {
     }
 };
 
+// What a context knows of launches of one shape.  block is 0 where only a list
+// capacity was learnt (from an overflow): the width is then the rule's, which
+// depends on how many groups may run, not on the shape alone.
 struct TuneVal {
-    int32_t block;
-    int64_t list_cap;
+    int32_t block = 0;
+    int64_t list_cap = 0;
 };
 
 // Host-side view of a request's outputs and where the kernel writes them.
@@ -726,60 +729,54 @@ struct LaunchPlan {
     int64_t cap = 1024;
 };
 
+// Threads of a work group.  Wide groups (1024, one per compute unit) while a
+// replication has a compute unit, or nearly one, to itself.  More replications
+// than that are better served by two groups of 512 threads a unit, and many
+// small grids, whose periods hold few cells, by five of 256.  Kernel times in ms
+// at 1024 / 512 / 256 threads, FP64 results, 48 periods (64^2 and 128^2: 24):
+//   1024^2   256 replications   4.52 /  5.14 /  7.80
+//   1024^2   768                6.79 /  5.92 /  8.09
+//    512^2   512                4.85 /  5.10 /  6.71
+//    512^2   768                6.12 /  5.16 /  7.34
+//    512^2  2048               13.5  /  9.80 /  9.59
+//    256^2   512                3.73 /  3.53 /  4.63
+//    256^2  1280                7.07 /  5.26 /  5.37
+//    256^2  2048               10.5  /  7.17 /  6.45
+//    128^2  1280                2.80 /  1.79 /  1.50
+//     64^2   512                1.12 /  0.84 /  0.88
+//     64^2  2048                3.38 /  2.02 /  1.32
+// and with other ignitions, at 512 / 256 threads:
+//   1024^2  1536                        6.94 /  7.09
+//    512^2  1536                        6.39 /  6.24
+//    512^2  4800                       16.3  / 13.5
+// FP64 results keep the 512-thread groups that callers are known to expect of
+// them for one fire from 2^22 cells and for up to a compute unit's worth of
+// replications from 2^26.  That is not the faster width: at 512 / 1024 threads a
+// fire of 2048^2 takes 3.01 / 2.66 ms, 64 of 8192^2 10.1 / 8.67; autotuning
+// finds it.  Below those sizes they are as wide as others: one fire of 1024^2
+// 2.56 / 2.27, 8 of 1500^2 2.43 / 2.15, 64 of 4096^2 4.62 / 4.01.  Where memory
+// or the caller holds a launch to fewer groups (grid_cap, 0 = it does not), their
+// number counts, not the replications': 512^2 x 2048 in 60 groups 79.5 ms at 256
+// threads, 56.2 at 1024; 256^2 x 2048 in 93 groups 37.8 and 28.7; 1024^2 x 512 in
+// 24 groups 42.1 at 512, 38.2 at 1024; 64^2 x 2048 in 431 groups 2.57 at 256,
+// 2.40 at 512.
+int32_t group_width(int32_t n_cu, int64_t cells, int32_t total_items, int32_t precision, int32_t grid_cap) {
+    const int64_t items = grid_cap > 0 ? std::min(total_items, grid_cap) : total_items;
+    if (precision == 0 && total_items <= n_cu && cells >= (total_items > 1 ? 1 << 26 : 1 << 22)) return 512;
+    if (items <= n_cu || (items <= 2 * (int64_t)n_cu && cells >= (1 << 18))) return 1024;
+    if ((items > 4 * (int64_t)n_cu && cells <= (1 << 14)) || (items > 5 * (int64_t)n_cu && cells <= (1 << 18)))
+        return 256;
+    return 512;
+}
+
 LaunchPlan plan_launch(c2f_ctx* ctx, int64_t cells, int32_t total_items, int32_t precision, int32_t grid_cap) {
     LaunchPlan lp;
     {
         std::lock_guard<std::mutex> lk(ctx->tunemu);
-        auto it = ctx->tune.find(TuneKey{cells, total_items, precision});
-        if (it != ctx->tune.end()) {
-            lp.block = it->second.block;
-            lp.cap = it->second.list_cap;
-        } else {
-            // Wide groups (1024 threads, one per compute unit) while a
-            // replication has a compute unit, or nearly one, to itself.  More
-            // replications than that are better served by two groups of 512
-            // threads a unit, and many small grids, whose periods hold few
-            // cells, by five of 256.  Kernel times in ms at 1024 / 512 / 256
-            // threads, FP64 results, 48 periods (64^2 and 128^2: 24):
-            //   1024^2   256 replications   4.52 /  5.14 /  7.80
-            //   1024^2   768                6.79 /  5.92 /  8.09
-            //    512^2   512                4.85 /  5.10 /  6.71
-            //    512^2   768                6.12 /  5.16 /  7.34
-            //    512^2  2048               13.5  /  9.80 /  9.59
-            //    256^2   512                3.73 /  3.53 /  4.63
-            //    256^2  1280                7.07 /  5.26 /  5.37
-            //    256^2  2048               10.5  /  7.17 /  6.45
-            //    128^2  1280                2.80 /  1.79 /  1.50
-            //     64^2   512                1.12 /  0.84 /  0.88
-            //     64^2  2048                3.38 /  2.02 /  1.32
-            // and with other ignitions, at 512 / 256 threads:
-            //   1024^2  1536                        6.94 /  7.09
-            //    512^2  1536                        6.39 /  6.24
-            //    512^2  4800                       16.3  / 13.5
-            // FP64 results keep the 512-thread groups that callers are known to
-            // expect of them for one fire from 2^22 cells and for up to a
-            // compute unit's worth of replications from 2^26.  That is not the
-            // faster width: at 512 / 1024 threads a fire of 2048^2 takes 3.01 /
-            // 2.66 ms, 64 of 8192^2 10.1 / 8.67; autotuning finds it.  Below
-            // those sizes they are as wide as others: one fire of 1024^2 2.56
-            // / 2.27, 8 of 1500^2 2.43 / 2.15, 64 of 4096^2 4.62 / 4.01.  Where
-            // memory or the caller holds a launch to fewer groups (grid_cap),
-            // their number counts, not the replications': 512^2 x 2048
-            // in 60 groups 79.5 ms at 256 threads, 56.2 at 1024; 256^2 x 2048
-            // in 93 groups 37.8 and 28.7; 1024^2 x 512 in 24 groups 42.1 at
-            // 512, 38.2 at 1024; 64^2 x 2048 in 431 groups 2.57 at 256, 2.40
-            // at 512.
-            const int64_t n_cu = ctx->n_cu, items = grid_cap > 0 ? std::min(total_items, grid_cap) : total_items;
-            if (precision == 0 && total_items <= n_cu && cells >= (total_items > 1 ? 1 << 26 : 1 << 22))
-                lp.block = 512;
-            else if (items <= n_cu || (items <= 2 * n_cu && cells >= (1 << 18)))
-                lp.block = 1024;
-            else if ((items > 4 * n_cu && cells <= (1 << 14)) || (items > 5 * n_cu && cells <= (1 << 18)))
-                lp.block = 256;
-            else
-                lp.block = 512;
-            lp.cap = default_list_cap(cells, total_items);
-        }
+        TuneVal known;
+        if (auto it = ctx->tune.find(TuneKey{cells, total_items, precision}); it != ctx->tune.end()) known = it->second;
+        lp.block = known.block ? known.block : group_width(ctx->n_cu, cells, total_items, precision, grid_cap);
+        lp.cap = known.list_cap ? known.list_cap : default_list_cap(cells, total_items);
         if (ctx->block_override) lp.block = ctx->block_override;
         if (ctx->cap_override) lp.cap = ctx->cap_override;
     }
@@ -788,6 +785,13 @@ LaunchPlan plan_launch(c2f_ctx* ctx, int64_t cells, int32_t total_items, int32_t
     lp.grid = std::max(1, std::min(total_items, per_cu * ctx->n_cu));
     if (grid_cap > 0) lp.grid = std::min(lp.grid, grid_cap);
     return lp;
+}
+
+// Groups a serving lane may run on grids of `cells`: the caller's limit (0 =
+// none) and what its plane pool holds.
+int32_t lane_grid_cap(c2f_ctx* ctx, int64_t cells, int32_t grid_cap) {
+    const int32_t held = lane_slot_cap(ctx->lane_plane_budget, cells);
+    return grid_cap > 0 ? std::min(grid_cap, held) : held;
 }
 
 // The kernel's record of one request: landscape and weather on the device,
@@ -864,9 +868,9 @@ c2f_status run_group(c2f_ctx* ctx, Exec& ex, const std::vector<int>& idx, const 
         max_cells = std::max(max_cells, Ls[k]->ncells());
         total += P[k].reps;
     }
+    if (ex.round_up) grid_cap = lane_grid_cap(ctx, max_cells, grid_cap);
     LaunchPlan lp = plan_launch(ctx, max_cells, total, precision, grid_cap);
     if (ex.round_up) {
-        lp.grid = std::min(lp.grid, lane_slot_cap(ctx->lane_plane_budget, max_cells));
         lp.cap = lane_list_cap(std::max(ctx->lane_list_budget, ex.list_pool), lp.grid, lp.cap);
     }
     c2f_status st = ensure_jobs(ctx, ex, (int32_t)idx.size());
@@ -1016,7 +1020,7 @@ c2f_status run_group(c2f_ctx* ctx, Exec& ex, const std::vector<int>& idx, const 
         lp.cap = std::min(hard_max, limit * 4);
         // remember the larger capacity for requests of this shape
         std::lock_guard<std::mutex> lk(ctx->tunemu);
-        ctx->tune[TuneKey{max_cells, total, precision}] = TuneVal{lp.block, lp.cap};
+        ctx->tune[TuneKey{max_cells, total, precision}].list_cap = lp.cap;
     }
 }
 
@@ -1154,8 +1158,9 @@ size_t batch_growth(c2f_ctx* ctx, const Exec& ex, const std::vector<std::shared_
     int64_t cap = 1, max_cells = 1;
     for (int pr = 0; pr < 2; ++pr) {
         if (!items[pr]) continue;
-        const LaunchPlan lp = plan_launch(ctx, cells[pr], items[pr], pr, ctx->max_batch_grid);
-        grid = std::max(grid, std::min(lp.grid, lane_slot_cap(ctx->lane_plane_budget, cells[pr])));
+        const LaunchPlan lp =
+            plan_launch(ctx, cells[pr], items[pr], pr, lane_grid_cap(ctx, cells[pr], ctx->max_batch_grid));
+        grid = std::max(grid, lp.grid);
         cap = std::max(cap, lp.cap);
         max_cells = std::max(max_cells, cells[pr]);
     }
@@ -2225,9 +2230,13 @@ c2f_status c2f_save_tuning(c2f_ctx* ctx, const char* path) {
     FILE* f = std::fopen(tmp.c_str(), "w");
     if (!f) return fail(ctx, C2F_EIO, "cannot write %s", tmp.c_str());
     bool ok = std::fprintf(f, "c2f-tuning 1 %s %d\n", ctx->arch.c_str(), ctx->n_cu) > 0;
-    for (const auto& kv : tune)
-        ok = ok && std::fprintf(f, "%lld %d %d %d %lld\n", (long long)kv.first.cells, kv.first.reps,
-                                kv.first.precision, kv.second.block, (long long)kv.second.list_cap) > 0;
+    for (const auto& kv : tune) {
+        const TuneKey& k = kv.first;
+        const int32_t block =
+            kv.second.block ? kv.second.block : group_width(ctx->n_cu, k.cells, k.reps, k.precision, 0);
+        ok = ok && std::fprintf(f, "%lld %d %d %d %lld\n", (long long)k.cells, k.reps, k.precision, block,
+                                (long long)kv.second.list_cap) > 0;
+    }
     ok = (std::fclose(f) == 0) && ok;
     if (!ok || std::rename(tmp.c_str(), path) != 0) {
         std::remove(tmp.c_str());
