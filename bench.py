@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("b51dad54ada9f231", 10_906_389),
-    "batched-mc-1024x1024-2048reps": ("b51dad54ada9f231", 45_087_348_522),
-    "large-8192x8192-64reps-72h": ("b51dad54ada9f231", 810_350_869),
+    "single-fire-2048x2048-48h": ("7fcf709e73f7acfd", 10_842_304),
+    "batched-mc-1024x1024-2048reps": ("7fcf709e73f7acfd", 45_114_706_496),
+    "large-8192x8192-64reps-72h": ("7fcf709e73f7acfd", 812_814_581),
 }
 
 

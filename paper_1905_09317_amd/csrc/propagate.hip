@@ -714,13 +714,16 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
                     // (in-grid burnable cells) excludes its axis.  Grids hold
                     // fewer than 2^31 cells.
                     const uint32_t cA = c + (uint32_t)offk, cB = c - (uint32_t)offk;
-                    const uint32_t own = load_label(&plane[c]);
+                    uint32_t own = load_label(&plane[c]);
                     const CellRec rec = load_rec(cells + c);
                     const uint32_t vA = plane[min(cA, last_cell)], vB = plane[min(cB, last_cell)];
                     // the random part while the loads are on their way
                     // (the empty asm keeps it there: it would sink to its use)
                     QuadDraws draws = quad_draws<sizeof(R) == 8>(erep, c, (uint32_t)p, role);
                     asm volatile("" : "+v"(draws.mu), "+v"(draws.w.n1), "+v"(draws.w.n2), "+v"(draws.w.wa), "+v"(draws.w.wb));
+                    // other waves lower the label meanwhile, and the quad's lanes
+                    // must agree on what follows: the first lane's load counts
+                    own = quad_lane<0>(own);
                     act = act && own == lab;
 
                     int32_t candA = kNever, candB = kNever;
