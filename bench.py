@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("7fcf709e73f7acfd", 10_842_304),
-    "batched-mc-1024x1024-2048reps": ("7fcf709e73f7acfd", 45_114_706_496),
-    "large-8192x8192-64reps-72h": ("7fcf709e73f7acfd", 812_814_581),
+    "single-fire-2048x2048-48h": ("2c29a90fa34434c2", 10_879_851),
+    "batched-mc-1024x1024-2048reps": ("2c29a90fa34434c2", 45_079_673_088),
+    "large-8192x8192-64reps-72h": ("2c29a90fa34434c2", 811_731_499),
 }
 
 

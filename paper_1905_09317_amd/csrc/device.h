@@ -251,18 +251,38 @@ struct CellRates {
     // form and its value jumps: f(W) at 40 km/h, grass LB at 1 km/h.  An
     // FP32 evaluation there may take the other branch than FP64.
     bool edge;
+    // (rates of a quad or a lane) how much further than usual an FP32
+    // evaluation may lie from FP64 here, 1 or more: grass whose wind and slope
+    // nearly cancel, since the direction of what is left, and a rate in front
+    // with it, carries their rounding, from WSV below 1 / kCancel of the wind;
+    // C-6 that starts to crown (c6_rate's gain), from kC6Gain
+    R widen;
 };
 
 constexpr float kEdgeWsv = 1e-3f;
+constexpr float kCancel = 16.0f;
+constexpr float kC6Gain = 6.0f;
+
+// CellRates::widen of a cell's wind; (wx, wy): the weather's part of it.
+template <typename R>
+__device__ __forceinline__ R widen_wind(R wsv, bool grass, R wx, R wy) {
+    const R w = (R)fabs(wx) + (R)fabs(wy), c = (R)kCancel * wsv;
+    return grass && c < w ? w * recip(c) : (R)1;
+}
 
 // C-6 crown fire: the surface rate rss at spread index isi becomes rss +
 // CFB (RSC - rss), RSC = 60 (1 - exp(-0.0497 ISI)) FME / 0.778 and CFB =
 // 1 - exp(-0.23 (rss - RSO)) above the critical surface rate RSO = CSI /
 // (300 SFC), 0 below it.
+// gain: how many times over the rate follows a relative change of rss and RSO,
+// where it crowns.
 template <typename R>
-__device__ __forceinline__ R c6_rate(R rss, R isi, R rso, R fme_r) {
+__device__ __forceinline__ R c6_rate(R rss, R isi, R rso, R fme_r, R& gain) {
     const R cfb = rss > rso ? -m_expm1((R)-0.23 * (rss - rso)) : (R)0;
-    return rss + cfb * ((R)60 * -m_expm1((R)-0.0497 * isi) * fme_r - rss);
+    const R lift = (R)60 * -m_expm1((R)-0.0497 * isi) * fme_r - rss;
+    const R r = rss + cfb * lift;
+    gain = rss > (R)0.9999 * rso ? (R)0.23 * ((R)1 - cfb) * (R)fabs(lift) * (rss + rso) * recip(r) : (R)0;
+    return r;
 }
 
 // Unit vector pointing upslope (east, north) from the Horn numerators.
@@ -323,8 +343,9 @@ __device__ __forceinline__ CellRates<R> cell_rates(const CoefR<R>* coef, const C
         if (f == kC6) {
             const R sfc = row[kRowSFC + kC6];
             const R rso = sfc > (R)0 ? L.csi[kC6] * recip((R)300 * sfc) : (R)3.0e38;
-            out.h = c6_rate<R>(out.rss, isi_h, rso, L.fme_r);
-            out.b = c6_rate<R>(out.b, isi_b, rso, L.fme_r);
+            R gain;
+            out.h = c6_rate<R>(out.rss, isi_h, rso, L.fme_r, gain);
+            out.b = c6_rate<R>(out.b, isi_b, rso, L.fme_r, gain);
         }
     }
     // LB - 1: grass 1.1 WSV^0.464 - 1 (0 below 1 km/h), other fuels
@@ -338,6 +359,7 @@ __device__ __forceinline__ CellRates<R> cell_rates(const CoefR<R>* coef, const C
     out.wy = wy;
     out.wsv = wsv;
     out.edge = fabs((double)wsv - 40.0) < (double)kEdgeWsv || (grass && fabs((double)wsv - 1.0) < (double)kEdgeWsv);
+    out.widen = (R)1;
     return out;
 }
 
@@ -455,16 +477,23 @@ static __constant__ CrownCoef kCrown[kNumFuels] = {C2F_CROWN_ROWS};
 // burned CFB = 1 - exp(-0.23 (S - RSO)) above the critical surface rate RSO
 // = CSI / (300 SFC) (S the head rate, the surface rate for C-6; 0 for fuels
 // that do not crown).  *cfb (may be NULL) receives CFB.
+// *steep (may be NULL): the fuel starts to crown and TFC follows a relative
+// change of S or RSO more than kHfiGain times over.
+constexpr float kHfiGain = 64.0f;
 template <typename R, typename LAND>
 __device__ __forceinline__ R head_intensity(const CellRates<R>& cr, int f, const R* row, const LAND& L,
-                                            R* cfb_out) {
+                                            R* cfb_out, bool* steep = nullptr) {
     R sfc = row[kRowSFC + f];
     if (is_mix_pc(f)) sfc = L.pc_w * row[kRowSFC + kC2] + ((R)1 - L.pc_w) * row[kRowSFC + kD1];
     const R cfl = (R)kCrown[f].cfl;
     R cfb = (R)0;
+    if (steep) *steep = false;
     if (cfl > (R)0 && sfc > (R)0) {
         const R rso = L.csi[f] * recip((R)300 * sfc);
         if (cr.rss > rso) cfb = -m_expm1((R)-0.23 * (cr.rss - rso));
+        if (steep)
+            *steep = cr.rss > (R)0.9999 * rso &&
+                     (R)0.23 * ((R)1 - cfb) * cfl * (cr.rss + rso) > (R)kHfiGain * (sfc + cfb * cfl);
     }
     if (cfb_out) *cfb_out = cfb;
     return (R)300 * (sfc + cfb * cfl) * cr.h;
@@ -579,21 +608,24 @@ __device__ __forceinline__ bool axis_q_direct(const RateCtx<R>& X, const CellRec
     return false;
 }
 
-// Integer rates of an FP64 context from an FP32 evaluation where that is
-// exact.  Away from the speeds where the model's form jumps (f(W) at 40
-// km/h, grass LB at 1 km/h), FP32 axis rates differ from the FP64 ones by
-// at most 7.0e-6 of max(1, x) over 630 M rates of the 1024^2 batched
-// landscape (its 16 fuel codes, 10 scenarios x 8 periods, noise, stochastic
-// rounding) and 9.4e-6 over 5 harsh landscapes (all 18 fuels, slopes above
-// 100 %, FFMC 80-99, BUI up to 250, winds up to 80 km/h), and head fire
-// intensities by at most 4.5e-5 relative.  So where x32 + u lies more than
-// kMixMargin max(1, x32) from an integer, floor(x64 + u) is the same
-// integer, and where the FP32 intensity lies more than kMixMarginH of the
-// threshold from it, the burn-out test agrees.  A cell whose FP32 wind
-// speed lies within kEdgeWsv of a jump (CellRates::edge), and every lane
-// where either test fails, takes the FP64 evaluation.  The margins leave a
-// factor of three or more over the measured differences; every FP64 parity
-// test compares the result with the FP64 oracle bit for bit.
+// Integer rates of an FP64 result from an FP32 evaluation where that is
+// exact: where x32 + u lies more than kMixMargin max(1, x32), times
+// CellRates::widen, from an integer, floor(x64 + u) is the same integer; and
+// where the FP32 intensity lies more than kMixMarginH of the threshold, widened
+// likewise, from it, the burn-out test agrees.  Every other cell, and one whose
+// CellRates::edge or head_intensity's steep is set, takes the FP64 evaluation.
+//
+// The FP32 evaluation reads the FP64 weather row rounded once.  (A row formed in
+// FP32 turned the wind by up to 3e-5 degrees, which a wind against a steep slope
+// magnifies, and lost the digits of C-1's consumption at low FFMC.)  Largest
+// differences from FP64, over widen, that a search found which climbs towards
+// them (6e10 cells: 18 fuels, slopes of up to 75 %, FFMC 40-101, BUI up to 300,
+// wind up to 400 km/h, seven sets of curing, foliar moisture from 1 to 300 %,
+// percent conifer and dead fir): 1.06e-5 of max(1, x) in grass, 9.6e-6 in C-6,
+// 3.9e-6 in the others; intensities 4.4e-5 relative.  With the library's functions
+// in place of MathFast's 9.5e-6, 9.1e-6, 3.8e-6 and 5.1e-5; with FP32 rows and
+// without widen and steep 1.0e-4, 1.7e-4, 1.9e-5 and 2.9e-2.  The margins are
+// 2.8 and 4.5 times the first figures.
 constexpr double kMixMargin = 3e-5;
 constexpr double kMixMarginH = 2e-4;
 
@@ -751,10 +783,13 @@ struct MathOf {
 // Largest errors over grids of 2^24 arguments, and those of the library's
 // FP32 functions: ln of the noise draw's u1, as the radius sqrt(-2 ln u1),
 // 4.9e-7 absolute (5.3e-7); the cosine 1.3e-7 absolute (0.5e-7); ln over
-// [1, 11] 1.6e-7 relative (1.6e-7); ln(1 - x) over (0, 0.99] 2.8e-7 relative
-// (2.7e-7); the square root 0.9e-7 relative; exp_wind over winds of 0 to 150
+// [1, 11] 1.6e-7 relative (1.6e-7); ln(1 - x) over (0, 0.99] 2.6e-7 relative
+// (2.6e-7); the square root 0.9e-7 relative; exp_wind over winds of 0 to 150
 // km/h 1.4e-7 relative (0.8e-7; 5.0e-7 without the correction of the
-// product's rounding).
+// product's rounding); exp_noise over [-10, 20] 1.3e-7 relative for each unit of
+// max(1, |x|) (0.8e-7); one_minus_exp over [1e-6, 40] 2.8e-7 relative (0.9e-7);
+// pow over bases of 1e-5 to 1 and the rate curves' exponents 2.3e-6 relative
+// (2.3e-6), 3.0e-7 (3.0e-7) over grass' winds.
 struct MathFast {
     static constexpr float kLog2e = 1.44269504088896340736f, kLog2eLow = 1.925963033e-8f;
     static constexpr float kLn2 = 0.69314718055994530942f;
@@ -766,7 +801,8 @@ struct MathFast {
     }
     static __device__ __forceinline__ float exp_noise(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
     // 1 - exp(-y), y >= 0: with u = exp(-y) rounded, 1 - u where u < 1/2, and
-    // above it (1 - u) y / -ln(u), which corrects the rounding of u
+    // above it (1 - u) y / -ln(u), which corrects the rounding of u (Kahan's
+    // form; Higham, Accuracy and Stability of Numerical Algorithms, 1.14.1)
     static __device__ __forceinline__ float one_minus_exp(float y) {
         const float p = y * -kLog2e;
         const float u = __builtin_amdgcn_exp2f(p);
@@ -869,11 +905,14 @@ __device__ __forceinline__ CellRates<R> quad_cell_rates(const EvalLds<R>& x, con
     r = r * x.row[kRowBE + f];
     CellRates<R> out;
     out.rss = quad_lane<0>(r);
+    out.widen = widen_wind<R>(wsv, grass, x.row[2], x.row[3]);
     if (__any(f == kC6)) {
         if (f == kC6) {
             const R sfc = x.row[kRowSFC + kC6];
             const R rso = sfc > (R)0 ? x.L.csi[kC6] * recip((R)300 * sfc) : (R)3.0e38;
-            r = c6_rate<R>(r, isi, rso, x.L.fme_r);
+            R gain;
+            r = c6_rate<R>(r, isi, rso, x.L.fme_r, gain);
+            out.widen = (R)fmax((R)1, (R)fmax(quad_lane<0>(gain), quad_lane<1>(gain)) * (R)(1.0f / kC6Gain));
         }
     }
     out.h = quad_lane<0>(r);
@@ -988,10 +1027,11 @@ static inline __device__ __attribute__((noinline)) QuadRates quad_axis_q_rare(co
 // FP32: its rounding, below 6.0e-8 (x + 1), and that of the distance from the
 // integer's middle widen kMixMargin by less than 2e-7 max(1, x).  Rates from
 // 16500 m/min up never pass.
-__device__ __forceinline__ int32_t quantise_mixed(float x, float u, bool& exact) {
+__device__ __forceinline__ float mix_margin(float widen) { return ((float)kMixMargin + 2e-7f) * widen; }
+__device__ __forceinline__ int32_t quantise_mixed(float x, float u, float margin, bool& exact) {
     const float v = x + u;
     const float k = floorf(v);
-    const float clear = fmaf(-((float)kMixMargin + 2e-7f), fmaxf(1.0f, x), 0.5f);
+    const float clear = fmaf(-margin, fmaxf(1.0f, x), 0.5f);
     exact = exact && fabsf((v - k) - 0.5f) < clear;
     return (int32_t)k;
 }
@@ -1036,13 +1076,16 @@ __device__ __forceinline__ bool quad_axis_q(const EvalLds<float>& x, const EvalL
         float xa, xb;
         quad_axis_rates<float, MathFast>(cr, mu, role, xa, xb);
         bool exact = !cr.edge;
-        qa = quantise_mixed(xa, e.rounding != 0 ? unit24<float>(w.wa) : 0.5f, exact);
-        qb = quantise_mixed(xb, e.rounding != 0 ? unit24<float>(w.wb) : 0.5f, exact);
+        const float margin = mix_margin(cr.widen);
+        qa = quantise_mixed(xa, e.rounding != 0 ? unit24<float>(w.wa) : 0.5f, margin, exact);
+        qb = quantise_mixed(xb, e.rounding != 0 ? unit24<float>(w.wb) : 0.5f, margin, exact);
         bool faint = false;
         if (e.hfi_min > 0.f) {
-            const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr) * mu);
+            bool steep;
+            const double hfi =
+                (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr, &steep) * mu);
             const double hm = (double)e.hfi_min;
-            exact = exact && fabs(hfi - hm) > kMixMarginH * hm;
+            exact = exact && !steep && fabs(hfi - hm) > kMixMarginH * (double)cr.widen * hm;
             faint = !(hfi >= hm);
         }
         // a NaN rate fails the comparison above and goes the FP64 way
@@ -1115,11 +1158,14 @@ __device__ __forceinline__ CellRates<float> lane_cell_rates(const EvalLds<float>
     b = b * be;
     CellRates<float> out;
     out.rss = h;
+    out.widen = widen_wind<float>(wsv, grass, x.row[2], x.row[3]);
     if (f == kC6) {
         const float sfc = x.row[kRowSFC + kC6];
         const float rso = sfc > 0.f ? x.L.csi[kC6] * recip(300.0f * sfc) : 3.0e38f;
-        h = c6_rate<float>(h, isi_h, rso, x.L.fme_r);
-        b = c6_rate<float>(b, isi_b, rso, x.L.fme_r);
+        float gain_h, gain_b;
+        h = c6_rate<float>(h, isi_h, rso, x.L.fme_r, gain_h);
+        b = c6_rate<float>(b, isi_b, rso, x.L.fme_r, gain_b);
+        out.widen = fmaxf(1.0f, fmaxf(gain_h, gain_b) * (1.0f / kC6Gain));
     }
     out.h = h;
     out.b = b;
@@ -1195,17 +1241,19 @@ __device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalR
     if constexpr (MIXED) done = done && !cr.edge;
     bool faint = false;
     if (e.hfi_min > 0.f) {
-        const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr) * mu);
+        bool steep;
+        const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr, &steep) * mu);
         const double hm = (double)e.hfi_min;
-        if constexpr (MIXED) done = done && fabs(hfi - hm) > kMixMarginH * hm;
+        if constexpr (MIXED) done = done && !steep && fabs(hfi - hm) > kMixMarginH * (double)cr.widen * hm;
         faint = !(hfi >= hm);
     }
     float x8[8];
     lane_axis_rates<M>(cr, mu, x8);
+    const float margin = MIXED ? mix_margin(cr.widen) : 0.0f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const float u = unit24<float>(w[k]);
-        if constexpr (MIXED) q[k] = quantise_mixed(x8[k], u, done);
+        if constexpr (MIXED) q[k] = quantise_mixed(x8[k], u, margin, done);
         else q[k] = quantise<float>(x8[k], u);
     }
     return faint;

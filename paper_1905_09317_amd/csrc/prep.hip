@@ -565,7 +565,7 @@ __global__ __launch_bounds__(256) void eval_q8_kernel(EvalArgs a) {
     }
     if (tid < kRowLen) {
         s_x64.row[tid] = a.table64[ro + tid];
-        s_x32.row[tid] = a.table32[ro + tid];
+        s_x32.row[tid] = sizeof(R) == 8 ? (float)a.table64[ro + tid] : a.table32[ro + tid];
     }
     if (tid == 0) s_e = e;
     __syncthreads();

@@ -309,7 +309,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
         const uint32_t pendv = (tag << kMinuteBits) | kPendingMinute;
         const size_t so = (size_t)scen_r * job.n_wp * kRowLen;
         const double* const g_rows64 = job.table64 + so;
-        const float* const g_rows32 = job.table32 + so;
+        const float* const g_rows32 = job.table32 + so;   // read for FP32 results only
         const EvalRep erep{job.seed, rep, job.rounding, job.sigma, job.hfi_min};
         const float burnout = job.burnout;
         // a global pointer: through a generic one each count would wait on
@@ -392,8 +392,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
             if (!burning_period(job, p)) continue;
             // every wave has left the previous period (its end barriers)
             for (int i = tid; i < kRowLen; i += BLOCK) {
-                s_x64.row[i] = g_rows64[(size_t)p * kRowLen + i];
-                s_x32.row[i] = g_rows32[(size_t)p * kRowLen + i];
+                const double t = g_rows64[(size_t)p * kRowLen + i];
+                s_x64.row[i] = t;
+                s_x32.row[i] = sizeof(R) == 8 ? (float)t : g_rows32[(size_t)p * kRowLen + i];
             }
             __syncthreads();
             const int32_t s = p * P + 1;   // first minute of period p
