@@ -626,8 +626,16 @@ __device__ __forceinline__ bool axis_q_direct(const RateCtx<R>& X, const CellRec
 // in place of MathFast's 9.5e-6, 9.1e-6, 3.8e-6 and 5.1e-5; with FP32 rows and
 // without widen and steep 1.0e-4, 1.7e-4, 1.9e-5 and 2.9e-2.  The margins are
 // 2.8 and 4.5 times the first figures.
+//
+// The noise multiplier exp(sigma z - sigma^2 / 2) adds to that: z may be off by
+// 4.9e-7 of its radius and 5.77 times 1.3e-7 of its cosine, and the exponent is
+// rounded three times at up to 5.77 sigma where the multiplier is not tiny (and
+// where it is, so is the rate).  That is below 2.3e-6 sigma; 1.4e-6 sigma was the
+// most over 3.4e8 draws at each of six sigma from 0.15 to 8 (1.3e-6 with the
+// library's functions).  Both margins grow by kMixSigma sigma.
 constexpr double kMixMargin = 3e-5;
 constexpr double kMixMarginH = 2e-4;
+constexpr double kMixSigma = 3e-6;
 
 template <typename R>
 __device__ __forceinline__ bool axis_q(const RateCtx<R>& X, const CellRec& rec, uint32_t cell, uint32_t period,
@@ -764,7 +772,18 @@ struct EvalRep {
     uint32_t rep;
     int32_t rounding;
     float sigma, hfi_min;
+    float margin;   // mix_margin(sigma)
 };
+// The rounding margin of a replication, the same in every lane: in a scalar
+// register (formed in every pass it made groups of 256 threads spill).
+__device__ __forceinline__ float mix_margin(float sigma) {
+    const float m = fmaf((float)kMixSigma, sigma, (float)kMixMargin + 2e-7f);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(m)));
+}
+// That of the head fire intensity.
+__device__ __forceinline__ double intensity_margin(const EvalRep& e) {
+    return (double)e.margin + (kMixMarginH - kMixMargin);
+}
 
 // The functions an evaluation uses: those of cell_rates and noise_mult, or
 // (FP32 only) the hardware's base-2 logarithm and exponential, square root and
@@ -1027,7 +1046,6 @@ static inline __device__ __attribute__((noinline)) QuadRates quad_axis_q_rare(co
 // FP32: its rounding, below 6.0e-8 (x + 1), and that of the distance from the
 // integer's middle widen kMixMargin by less than 2e-7 max(1, x).  Rates from
 // 16500 m/min up never pass.
-__device__ __forceinline__ float mix_margin(float widen) { return ((float)kMixMargin + 2e-7f) * widen; }
 __device__ __forceinline__ int32_t quantise_mixed(float x, float u, float margin, bool& exact) {
     const float v = x + u;
     const float k = floorf(v);
@@ -1076,7 +1094,7 @@ __device__ __forceinline__ bool quad_axis_q(const EvalLds<float>& x, const EvalL
         float xa, xb;
         quad_axis_rates<float, MathFast>(cr, mu, role, xa, xb);
         bool exact = !cr.edge;
-        const float margin = mix_margin(cr.widen);
+        const float margin = e.margin * cr.widen;
         qa = quantise_mixed(xa, e.rounding != 0 ? unit24<float>(w.wa) : 0.5f, margin, exact);
         qb = quantise_mixed(xb, e.rounding != 0 ? unit24<float>(w.wb) : 0.5f, margin, exact);
         bool faint = false;
@@ -1085,7 +1103,7 @@ __device__ __forceinline__ bool quad_axis_q(const EvalLds<float>& x, const EvalL
             const double hfi =
                 (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr, &steep) * mu);
             const double hm = (double)e.hfi_min;
-            exact = exact && !steep && fabs(hfi - hm) > kMixMarginH * (double)cr.widen * hm;
+            exact = exact && !steep && fabs(hfi - hm) > intensity_margin(e) * (double)cr.widen * hm;
             faint = !(hfi >= hm);
         }
         // a NaN rate fails the comparison above and goes the FP64 way
@@ -1244,12 +1262,12 @@ __device__ __forceinline__ bool lane_axis_q(const EvalLds<float>& x, const EvalR
         bool steep;
         const double hfi = (double)(head_intensity(cr, rec_fuel(rec.info), x.row, x.L, (float*)nullptr, &steep) * mu);
         const double hm = (double)e.hfi_min;
-        if constexpr (MIXED) done = done && !steep && fabs(hfi - hm) > kMixMarginH * (double)cr.widen * hm;
+        if constexpr (MIXED) done = done && !steep && fabs(hfi - hm) > intensity_margin(e) * (double)cr.widen * hm;
         faint = !(hfi >= hm);
     }
     float x8[8];
     lane_axis_rates<M>(cr, mu, x8);
-    const float margin = MIXED ? mix_margin(cr.widen) : 0.0f;
+    const float margin = MIXED ? e.margin * cr.widen : 0.0f;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
         const float u = unit24<float>(w[k]);

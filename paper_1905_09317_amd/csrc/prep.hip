@@ -552,7 +552,7 @@ __global__ __launch_bounds__(256) void eval_q8_kernel(EvalArgs a) {
     __shared__ EvalLds<double> s_x64;
     __shared__ EvalLds<float> s_x32;
     __shared__ EvalRep s_e;
-    const EvalRep e{a.seed, a.rep, a.rounding, a.sigma, 0.f};
+    const EvalRep e{a.seed, a.rep, a.rounding, a.sigma, 0.f, mix_margin(a.sigma)};
     const int tid = (int)threadIdx.x, role = tid & 3;
     const size_t ro = ((size_t)a.scenario * a.n_wp + a.period) * kRowLen;
     if (tid < kNumCurves) {
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(256) void eval_q8_kernel(EvalArgs a) {
     }
     if (tid < kRowLen) {
         s_x64.row[tid] = a.table64[ro + tid];
-        s_x32.row[tid] = sizeof(R) == 8 ? (float)a.table64[ro + tid] : a.table32[ro + tid];
+        s_x32.row[tid] = (float)((const R*)a.table)[ro + tid];
     }
     if (tid == 0) s_e = e;
     __syncthreads();

@@ -281,7 +281,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
             rep_draws(job, rep, scen, ign);
             s_scen = scen;
             s_ign = ign;
-            s_e = EvalRep{job.seed, rep, job.rounding, job.sigma, job.hfi_min};
+            s_e = EvalRep{job.seed, rep, job.rounding, job.sigma, job.hfi_min, 0.f};
         }
         __syncthreads();
         if (s_refill) {
@@ -309,8 +309,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
         const uint32_t pendv = (tag << kMinuteBits) | kPendingMinute;
         const size_t so = (size_t)scen_r * job.n_wp * kRowLen;
         const double* const g_rows64 = job.table64 + so;
-        const float* const g_rows32 = job.table32 + so;   // read for FP32 results only
-        const EvalRep erep{job.seed, rep, job.rounding, job.sigma, job.hfi_min};
+        const R* const g_rows = (const R*)job.table + so;   // in the precision of the results
+        const EvalRep erep{job.seed, rep, job.rounding, job.sigma, job.hfi_min, mix_margin(job.sigma)};
         const float burnout = job.burnout;
         // a global pointer: through a generic one each count would wait on
         // LDS and memory both
@@ -392,9 +392,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 5 : 4) void propagate_kernel(
             if (!burning_period(job, p)) continue;
             // every wave has left the previous period (its end barriers)
             for (int i = tid; i < kRowLen; i += BLOCK) {
-                const double t = g_rows64[(size_t)p * kRowLen + i];
-                s_x64.row[i] = t;
-                s_x32.row[i] = sizeof(R) == 8 ? (float)t : g_rows32[(size_t)p * kRowLen + i];
+                s_x64.row[i] = g_rows64[(size_t)p * kRowLen + i];
+                s_x32.row[i] = (float)g_rows[(size_t)p * kRowLen + i];
             }
             __syncthreads();
             const int32_t s = p * P + 1;   // first minute of period p

@@ -46,41 +46,65 @@ RATES = {
 }
 
 
+def _wrong_at_boundaries(sim, land, row, col, lo, hi, cell, what, **kw):
+    """(rates looked at, those that are not the floor of the FP64 rate) of one
+    cell, the weather value `col` stepped through the floats around every
+    rounding boundary between lo and hi."""
+    def rates(values):
+        wx = np.tile(np.float32(row), (len(values), 1))
+        wx[:, col] = values
+        w = sim.set_weather(wx[:, None, :])
+        out = [sim.eval_ros(land, w, scenario=k, precision=0, **kw) for k in range(len(values))]
+        sim.unset_weather(w)
+        return np.array([o["x8"][cell] for o in out]), np.array([o["q8"][cell] for o in out])
+
+    grid = np.linspace(lo, hi, 120).astype(np.float32)
+    f = rates(grid)[0] + 0.5
+    at = []
+    for k, a in zip(*np.nonzero(np.floor(f[1:]) != np.floor(f[:-1]))):
+        b = max(np.floor(f[k, a]), np.floor(f[k + 1, a]))
+        at.append(np.float32(grid[k] + (grid[k + 1] - grid[k]) * (b - f[k, a]) / (f[k + 1, a] - f[k, a])))
+    at = at[:: max(1, len(at) // 60)]
+    print(f"rounding boundaries: {what}, {kw}, {len(at)} crossings", flush=True)
+    if not at:
+        return 0, []
+    values = np.concatenate([t + np.arange(-24, 25) * np.spacing(t) * 8 for t in at]).astype(np.float32)
+    x, q = rates(values)
+    return q.size, [(float(values[k]), int(a), float(x[k, a]), int(q[k, a]))
+                    for k, a in np.argwhere(q != np.floor(x + 0.5))]
+
+
 @pytest.mark.parametrize("name", RATES)
 @pytest.mark.parametrize("sigma", [0.0, 2.5])
 def test_rates_at_rounding_boundaries(sim, name, sigma):
     fuel, row, grad, (pc, curing, fmc, pdf), col, (lo, hi) = RATES[name]
     land = sim.load_landscape(np.full((3, 3), fuel, np.uint8), _elevation(*grad), cell_m=1000, pc=pc, curing=curing)
     sim.set_landscape_fbp(land, fmc=fmc, pdf=pdf)
-
-    def rates(values, rep):
-        wx = np.tile(np.float32(row), (len(values), 1))
-        wx[:, col] = values
-        w = sim.set_weather(wx[:, None, :])
-        out = [sim.eval_ros(land, w, scenario=k, rep=rep, seed=3, sigma=sigma, precision=0) for k in range(len(values))]
-        sim.unset_weather(w)
-        return np.array([o["x8"][4] for o in out]), np.array([o["q8"][4] for o in out])
-
     n, bad = 0, []
     for rep in range(1 if sigma == 0.0 else 4):
-        grid = np.linspace(lo, hi, 120).astype(np.float32)
-        x, _ = rates(grid, rep)
-        f = x + 0.5
-        at = []
-        for k, a in zip(*np.nonzero(np.floor(f[1:]) != np.floor(f[:-1]))):
-            b = max(np.floor(f[k, a]), np.floor(f[k + 1, a]))
-            t = grid[k] + (grid[k + 1] - grid[k]) * (b - f[k, a]) / (f[k + 1, a] - f[k, a])
-            at.append(np.float32(t))
-        at = at[:: max(1, len(at) // 60)]
-        step = np.arange(-24, 25)
-        values = np.concatenate([t + step * np.spacing(t) * 8 for t in at]).astype(np.float32) if at else grid[:0]
-        print(f"rounding boundaries: {name}, sigma {sigma}, {len(at)} crossings", flush=True)
-        if len(values) == 0:
-            continue
-        x, q = rates(values, rep)
-        wrong = np.argwhere(q != np.floor(x + 0.5))
-        n += q.size
-        bad += [(float(values[k]), int(a), float(x[k, a]), int(q[k, a])) for k, a in wrong]
+        m, wrong = _wrong_at_boundaries(sim, land, row, col, lo, hi, 4, name, rep=rep, seed=3, sigma=sigma)
+        n, bad = n + m, bad + wrong
+    sim.unload_landscape(land)
+    assert n > 0 and not bad, (len(bad), n, bad[:4])
+
+
+@pytest.mark.parametrize("sigma", [1.0, 4.0, 7.0])
+def test_rates_of_rare_draws_at_rounding_boundaries(sim, sigma):
+    """The cells of 64 x 64 whose noise draws lie furthest out and whose rates
+    are still of middling size."""
+    land = sim.load_landscape(np.full((64, 64), 2, np.uint8))
+    row = (92.0, 80.0, 25.0, 240.0)
+    w = sim.set_weather(np.float32([[row]]))
+    found = []
+    for rep in range(40):
+        top = sim.eval_ros(land, w, rep=rep, seed=9, sigma=sigma)["x8"].max(axis=1)
+        for c in np.flatnonzero((top > 1.0) & (top < 2000.0)):
+            found.append((float(top[c]), rep, int(c)))
+    sim.unset_weather(w)
+    n, bad = 0, []
+    for _, rep, cell in sorted(found)[-6:]:
+        m, wrong = _wrong_at_boundaries(sim, land, row, 1, 60.0, 100.0, cell, "rare draws", rep=rep, seed=9, sigma=sigma)
+        n, bad = n + m, bad + wrong
     sim.unload_landscape(land)
     assert n > 0 and not bad, (len(bad), n, bad[:4])
 
