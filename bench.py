@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("c4cef0b92daddc82", 10_896_661),
-    "batched-mc-1024x1024-2048reps": ("c4cef0b92daddc82", 44_998_267_350),
-    "large-8192x8192-64reps-72h": ("c4cef0b92daddc82", 811_231_403),
+    "single-fire-2048x2048-48h": ("86776a2cf699b20a", 10_895_478),
+    "batched-mc-1024x1024-2048reps": ("86776a2cf699b20a", 45_011_482_741),
+    "large-8192x8192-64reps-72h": ("86776a2cf699b20a", 811_516_875),
 }
 
 

@@ -11,8 +11,12 @@
 // Once every arrival minute is known, each burned cell's own walk is fixed:
 // in each period it advances every axis whose neighbour is still available
 // (arrival at or after the minute) at its integer rates, so one thread per
-// (replication, cell) replays it period by period, with the same rate code
-// as the propagation kernel.  Used to measure algorithmic bytes; not on the
+// (replication, cell) replays it period by period.  FP64 results: every rate is
+// evaluated in FP64 here, since the threads of a wave are in different periods
+// and the propagation's FP32 evaluation reads a period's weather from LDS (8192^2
+// x 64 replications 40 -> 43 ms, 1024^2 x 2048 56 -> 65 against an FP32
+// evaluation from the FP32 table, which gave other counts than the fire's rates
+// near rounding boundaries).  Used to measure algorithmic bytes; not on the
 // simulation path.
 
 #include <hip/hip_runtime.h>
@@ -32,13 +36,11 @@ __global__ __launch_bounds__(256) void work_counts_kernel(const Job* __restrict_
                                                           unsigned long long* __restrict__ out) {
     __shared__ CoefR<R> s_coef[kNumFuels];
     __shared__ CoefR<double> s_coef64[kNumFuels];
-    __shared__ CoefR<float> s_coef32[kNumFuels];
     __shared__ unsigned long long s_sum[3];
     const int tid = threadIdx.x;
     if (tid < kNumFuels) {
         s_coef[tid] = coef_table<R>()[tid];
         s_coef64[tid] = coef_table<double>()[tid];
-        s_coef32[tid] = coef_table<float>()[tid];
     }
     if (tid < 3) s_sum[tid] = 0ull;
     __syncthreads();
@@ -81,15 +83,10 @@ __global__ __launch_bounds__(256) void work_counts_kernel(const Job* __restrict_
         X.L64 = land_consts<double>(job.land);
         X.rows = (const R*)job.table + (size_t)scen * job.n_wp * kRowLen;
         X.rows64 = job.table64 + (size_t)scen * job.n_wp * kRowLen;
-        X.row_stride = kRowLen;
-        X.coef32 = s_coef32;
-        X.L32 = land_consts<float>(job.land);
-        X.rows32 = job.table32 ? job.table32 + (size_t)scen * job.n_wp * kRowLen : nullptr;
         X.seed = job.seed;
         X.sigma = (R)job.sigma;
         X.rounding = job.rounding;
         X.rep = rep;
-        X.burnout = job.burnout;
         X.hfi_min = job.hfi_min;
         int32_t prog[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         // the cell first spreads in minute a + 1, which lies in period a / P

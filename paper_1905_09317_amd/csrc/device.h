@@ -499,8 +499,9 @@ __device__ __forceinline__ R head_intensity(const CellRates<R>& cr, int f, const
     return (R)300 * (sfc + cfb * cfl) * cr.h;
 }
 
-// Everything a rate evaluation needs besides the cell: coefficient tables,
-// landscape constants, the scenario's weather rows and the random stream.
+// What the evaluation of one cell by one thread needs besides the cell:
+// coefficient tables, landscape constants, the scenario's weather rows and the
+// random stream.
 template <typename R>
 struct RateCtx {
     const CoefR<R>* coef;
@@ -509,21 +510,11 @@ struct RateCtx {
     LandR<double> L64;
     const R* rows;          // first row of the replication's scenario
     const double* rows64;
-    // elements from one period's row to the next: kRowLen, or 0 where
-    // rows, rows64 and rows32 hold only the period being evaluated
-    uint32_t row_stride;
     uint64_t seed;
     R sigma;
     int rounding;
     uint32_t rep;
-    float burnout;   // burn-out threshold on the integer axis rates (0 = off)
     float hfi_min;   // burn-out threshold on the head fire intensity, kW/m (0 = off)
-    // FP32 coefficient table, landscape constants and weather rows of the
-    // same scenario: an FP64 context tries them first (axis_q).  rows32
-    // NULL: FP64 only.
-    const CoefR<float>* coef32;
-    LandR<float> L32;
-    const float* rows32;
 };
 
 // Weather scenario and ignition cell of replication `rep` of a job
@@ -590,9 +581,9 @@ __device__ __forceinline__ bool seeds_at(const Job& job, int p) {
 // an intensity threshold is set and the intensity, with the noise
 // multiplier on the rate, is below it.
 template <typename R>
-__device__ __forceinline__ bool axis_q_direct(const RateCtx<R>& X, const CellRec& rec, uint32_t cell,
-                                              uint32_t period, int32_t* q) {
-    const size_t ro = (size_t)period * X.row_stride;
+__device__ __forceinline__ bool axis_q(const RateCtx<R>& X, const CellRec& rec, uint32_t cell, uint32_t period,
+                                       int32_t* q) {
+    const size_t ro = (size_t)period * kRowLen;
     const CellRates<R> cr = cell_rates<R>(X.coef, X.coef64, rec, X.rows + ro, X.rows64 + ro, X.L, X.L64);
     const R mu = noise_mult<R>(X.seed, cell, period, X.rep, X.sigma);
     uint4 ua = make_uint4(0u, 0u, 0u, 0u), ub = ua;
@@ -637,51 +628,10 @@ constexpr double kMixMargin = 3e-5;
 constexpr double kMixMarginH = 2e-4;
 constexpr double kMixSigma = 3e-6;
 
-template <typename R>
-__device__ __forceinline__ bool axis_q(const RateCtx<R>& X, const CellRec& rec, uint32_t cell, uint32_t period,
-                                       int32_t* q) {
-    if constexpr (sizeof(R) == 8) {
-        if (X.rows32 != nullptr) {
-            const size_t ro = (size_t)period * X.row_stride;
-            const CellRates<float> cr =
-                cell_rates<float>(X.coef32, X.coef64, rec, X.rows32 + ro, X.rows64 + ro, X.L32, X.L64);
-            const float mu = noise_mult<float>(X.seed, cell, period, X.rep, (float)X.sigma);
-            uint4 ua = make_uint4(0u, 0u, 0u, 0u), ub = ua;
-            if (X.rounding != 0) {
-                ua = draw(X.seed, cell, period, X.rep, 1u);
-                ub = draw(X.seed, cell, period, X.rep, 2u);
-            }
-            float x[8];
-            axis_rates<float>(cr, mu, x);
-            const uint32_t w[8] = {ua.x, ua.y, ua.z, ua.w, ub.x, ub.y, ub.z, ub.w};
-            bool exact = !cr.edge;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const double u = X.rounding != 0 ? unit24<double>(w[k]) : 0.5;
-                const double v = (double)x[k] + u;
-                const double m = kMixMargin * fmax(1.0, (double)x[k]);
-                const double lo = floor(v - m);
-                exact = exact && lo == floor(v + m);
-                q[k] = (lo < 1073741824.0) ? (int32_t)lo : 1073741824;
-            }
-            bool faint = false;
-            if (X.hfi_min > 0.f) {
-                const double hfi =
-                    (double)(head_intensity(cr, rec_fuel(rec.info), X.rows32 + ro, X.L32, (float*)nullptr) * mu);
-                const double hm = (double)X.hfi_min;
-                exact = exact && fabs(hfi - hm) > kMixMarginH * hm;
-                faint = !(hfi >= hm);
-            }
-            if (exact) return faint;
-        }
-    }
-    return axis_q_direct<R>(X, rec, cell, period, q);
-}
-
 // Head rate times the noise multiplier: the receiving cell's ignition test.
 template <typename R>
 __device__ __forceinline__ R head_rate(const RateCtx<R>& X, const CellRec& rec, uint32_t cell, uint32_t period) {
-    const size_t ro = (size_t)period * X.row_stride;
+    const size_t ro = (size_t)period * kRowLen;
     const CellRates<R> cr = cell_rates<R>(X.coef, X.coef64, rec, X.rows + ro, X.rows64 + ro, X.L, X.L64);
     return cr.h * noise_mult<R>(X.seed, cell, period, X.rep, X.sigma);
 }

@@ -51,15 +51,10 @@ __global__ __launch_bounds__(256) void order_keys_kernel(const Job* __restrict__
     X.L64 = land_consts<double>(job.land);
     X.rows = (const R*)job.table + (size_t)scen * job.n_wp * kRowLen;
     X.rows64 = job.table64 + (size_t)scen * job.n_wp * kRowLen;
-    X.row_stride = kRowLen;
-    X.coef32 = coef_table<float>();
-    X.L32 = land_consts<float>(job.land);
-    X.rows32 = job.table32 ? job.table32 + (size_t)scen * job.n_wp * kRowLen : nullptr;
     X.seed = job.seed;
     X.sigma = (R)job.sigma;
     X.rounding = job.rounding;
     X.rep = rep;
-    X.burnout = 0.f;
     X.hfi_min = 0.f;
     const R h = head_rate<R>(X, rec, (uint32_t)ign, (uint32_t)p) * (R)job.period_min;
     // at most 2^20 m per period keeps the sum of up to 2^31 periods in 64 bits

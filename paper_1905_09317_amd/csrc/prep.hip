@@ -485,24 +485,13 @@ hipError_t launch_weather_table(const float* wx, int n_rows, double* t64, float*
 
 template <typename R>
 __global__ void eval_ros_kernel(EvalArgs a) {
-    RateCtx<R> X;
-    X.coef = coef_table<R>();
-    X.coef64 = coef_table<double>();
-    X.L = land_consts<R>(a.land);
-    X.L64 = land_consts<double>(a.land);
-    X.rows = (const R*)a.table + (size_t)a.scenario * a.n_wp * kRowLen;
-    X.rows64 = a.table64 + (size_t)a.scenario * a.n_wp * kRowLen;
-    X.row_stride = kRowLen;
-    X.coef32 = coef_table<float>();
-    X.L32 = land_consts<float>(a.land);
-    X.rows32 = a.table32 ? a.table32 + (size_t)a.scenario * a.n_wp * kRowLen : nullptr;
-    X.seed = a.seed;
-    X.sigma = (R)a.sigma;
-    X.rounding = a.rounding;
-    X.rep = a.rep;
-    X.burnout = 0.f;
-    X.hfi_min = 0.f;
-    const size_t ro = (size_t)a.period * kRowLen;
+    const CoefR<R>* const coef = coef_table<R>();
+    const CoefR<double>* const coef64 = coef_table<double>();
+    const LandR<R> L = land_consts<R>(a.land);
+    const LandR<double> L64 = land_consts<double>(a.land);
+    const size_t ro = ((size_t)a.scenario * a.n_wp + a.period) * kRowLen;
+    const R* const row = (const R*)a.table + ro;
+    const double* const row64 = a.table64 + ro;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n_cells; i += gridDim.x * blockDim.x) {
         const CellRec rec = a.cells[i];
         const int f = rec_fuel(rec.info);
@@ -518,7 +507,7 @@ __global__ void eval_ros_kernel(EvalArgs a) {
                 if (a.x8) a.x8[(size_t)i * 8 + k] = 0;
             continue;
         }
-        const CellRates<R> cr = cell_rates<R>(X.coef, X.coef64, rec, X.rows + ro, X.rows64 + ro, X.L, X.L64);
+        const CellRates<R> cr = cell_rates<R>(coef, coef64, rec, row, row64, L, L64);
         const R mu = noise_mult<R>(a.seed, (uint32_t)i, (uint32_t)a.period, a.rep, (R)a.sigma);
         R x[8];
         axis_rates<R>(cr, mu, x);
@@ -528,7 +517,7 @@ __global__ void eval_ros_kernel(EvalArgs a) {
         if (a.lb) a.lb[i] = (double)cr.lb;
         if (a.cfb || a.hfi) {
             R cfb = (R)0;
-            const R hfi = head_intensity(cr, f, X.rows + ro, X.L, &cfb) * mu;
+            const R hfi = head_intensity(cr, f, row, L, &cfb) * mu;
             if (a.cfb) a.cfb[i] = (double)cfb;
             if (a.hfi) a.hfi[i] = (double)hfi;
         }
