@@ -382,6 +382,18 @@ void exec_trim(c2f_ctx* ctx, Exec& ex) {
     ex.d_jobs_cap = 0;
 }
 
+// dev_alloc for what is not an executor's (caller holds ctx->mu, no launch of
+// the main executor is being made up): if memory is short, the planes and lists
+// that executor keeps for its next launch are given back first.  A launch of many
+// small replications keeps five slots a compute unit, several GB.
+c2f_status resident_alloc(c2f_ctx* ctx, void** p, size_t bytes) {
+    c2f_status st = dev_alloc(ctx, p, bytes);
+    if (st != C2F_ENOMEM || (!ctx->main.planes && !ctx->main.lists && !ctx->main.staging)) return st;
+    exec_trim(ctx, ctx->main);
+    t_err.clear();
+    return dev_alloc(ctx, p, bytes);
+}
+
 void exec_release(c2f_ctx* ctx, Exec& ex) {
     exec_trim(ctx, ex);
     dev_free(ctx, ex.rc, sizeof(RunCounters));
@@ -632,6 +644,16 @@ c2f_status ensure_staging(c2f_ctx* ctx, Exec& ex, size_t bytes) {
         ex.staging_bytes = alloc;
     }
     return C2F_OK;
+}
+
+// Staging of a call that has not taken its slots yet: if memory is short, the
+// executor's buffers of earlier launches are given back first.
+c2f_status staging_room(c2f_ctx* ctx, Exec& ex, size_t bytes) {
+    c2f_status st = ensure_staging(ctx, ex, bytes);
+    if (st != C2F_ENOMEM || (!ex.planes && !ex.lists)) return st;
+    exec_trim(ctx, ex);
+    t_err.clear();
+    return ensure_staging(ctx, ex, bytes);
 }
 
 // Pinned host memory the device staging is copied into in one transfer;
@@ -1070,7 +1092,7 @@ c2f_status run_requests(c2f_ctx* ctx, Exec& ex, const std::vector<c2f_sim_params
                        need(o.scenario, r * 4)};
         }
     }
-    c2f_status st = ensure_staging(ctx, ex, stage);
+    c2f_status st = staging_room(ctx, ex, stage);
     if (st != C2F_OK) return st;
     char* sb = (char*)ex.staging;
     for (int k = 0; k < n_jobs; ++k) {
@@ -1510,12 +1532,12 @@ c2f_status c2f_load_landscape(c2f_ctx* ctx, int32_t rows, int32_t cols, int32_t 
         dev_free(ctx, d_elev, (size_t)n * 2);
         dev_free(ctx, d_tiles, (size_t)n_tiles * 4);
     };
-    if ((st = dev_alloc(ctx, (void**)&L.fuel, (size_t)n)) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.cells, (size_t)n * sizeof(CellRec))) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.burnable, (size_t)n * 4)) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.land, sizeof(LandDev))) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&d_tiles, (size_t)n_tiles * 4)) != C2F_OK ||
-        (elev_m && (st = dev_alloc(ctx, (void**)&d_elev, (size_t)n * 2)) != C2F_OK)) {
+    if ((st = resident_alloc(ctx, (void**)&L.fuel, (size_t)n)) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.cells, (size_t)n * sizeof(CellRec))) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.burnable, (size_t)n * 4)) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.land, sizeof(LandDev))) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&d_tiles, (size_t)n_tiles * 4)) != C2F_OK ||
+        (elev_m && (st = resident_alloc(ctx, (void**)&d_elev, (size_t)n * 2)) != C2F_OK)) {
         cleanup();
         return st;
     }
@@ -1603,11 +1625,11 @@ c2f_status c2f_derive_landscape(c2f_ctx* ctx, int32_t base_id, int64_t n_edits, 
         dev_free(ctx, L.land, sizeof(LandDev));
     };
     c2f_status st = C2F_OK;
-    if ((st = dev_alloc(ctx, (void**)&L.fuel, (size_t)n)) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.cells, (size_t)n * sizeof(CellRec))) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.burnable, (size_t)n * 4)) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&L.land, sizeof(LandDev))) != C2F_OK ||
-        (st = dev_alloc(ctx, (void**)&d_tiles, (size_t)n_tiles * 4)) != C2F_OK) {
+    if ((st = resident_alloc(ctx, (void**)&L.fuel, (size_t)n)) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.cells, (size_t)n * sizeof(CellRec))) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.burnable, (size_t)n * 4)) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&L.land, sizeof(LandDev))) != C2F_OK ||
+        (st = resident_alloc(ctx, (void**)&d_tiles, (size_t)n_tiles * 4)) != C2F_OK) {
         cleanup();
         return st;
     }
@@ -1695,7 +1717,7 @@ c2f_status scar_buffers(c2f_ctx* ctx, size_t T, hipStream_t s, unsigned long lon
             ctx->metric_bytes = 0;
             ctx->metric_periods = 0;
         }
-        const c2f_status st = dev_alloc(ctx, &ctx->metric_buf, need);
+        const c2f_status st = resident_alloc(ctx, &ctx->metric_buf, need);
         if (st != C2F_OK) return st;
         ctx->metric_bytes = need;
         const size_t zero_bytes = ((C * 24 + 255) & ~(size_t)255) + 256;
@@ -1742,8 +1764,8 @@ c2f_status c2f_compare_scars(c2f_ctx* ctx, int64_t n_cells, int32_t n_periods, i
     if (on_device) {
         d_arr = const_cast<int32_t*>(arrival_minute);
         d_ref = const_cast<uint8_t*>(reference);
-    } else if ((st = dev_alloc(ctx, (void**)&d_arr, n * 4)) != C2F_OK ||
-               (st = dev_alloc(ctx, (void**)&d_ref, n * T)) != C2F_OK) {
+    } else if ((st = resident_alloc(ctx, (void**)&d_arr, n * 4)) != C2F_OK ||
+               (st = resident_alloc(ctx, (void**)&d_ref, n * T)) != C2F_OK) {
         cleanup();
         return st;
     }
@@ -1814,7 +1836,7 @@ c2f_status c2f_set_ignition_map(c2f_ctx* ctx, int32_t landscape_id, const uint32
         cdf[i] = run;
     }
     uint64_t* d = nullptr;
-    c2f_status st = dev_alloc(ctx, (void**)&d, n * 8);
+    c2f_status st = resident_alloc(ctx, (void**)&d, n * 8);
     if (st != C2F_OK) return st;
     if (hipMemcpy(d, cdf.data(), n * 8, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipGetLastError();
@@ -1848,12 +1870,12 @@ c2f_status c2f_set_weather(c2f_ctx* ctx, int32_t n_scen, int32_t n_periods, int3
     W.n_periods = n_periods;
     W.period_min = period_min;
     c2f_status st;
-    if ((st = dev_alloc(ctx, (void**)&W.rows, (size_t)nr * 16)) != C2F_OK) return st;
-    if ((st = dev_alloc(ctx, (void**)&W.t64, (size_t)nr * kRowLen * 8)) != C2F_OK) {
+    if ((st = resident_alloc(ctx, (void**)&W.rows, (size_t)nr * 16)) != C2F_OK) return st;
+    if ((st = resident_alloc(ctx, (void**)&W.t64, (size_t)nr * kRowLen * 8)) != C2F_OK) {
         dev_free(ctx, W.rows, (size_t)nr * 16);
         return st;
     }
-    if ((st = dev_alloc(ctx, (void**)&W.t32, (size_t)nr * kRowLen * 4)) != C2F_OK) {
+    if ((st = resident_alloc(ctx, (void**)&W.t32, (size_t)nr * kRowLen * 4)) != C2F_OK) {
         dev_free(ctx, W.rows, (size_t)nr * 16);
         dev_free(ctx, W.t64, (size_t)nr * kRowLen * 8);
         return st;
@@ -2006,7 +2028,7 @@ c2f_status c2f_count_work(c2f_ctx* ctx, const c2f_sim_params* params, const int3
     if (st != C2F_OK) return st;
     const size_t job_off = 256;
     if (!ctx->acct) {
-        st = dev_alloc(ctx, &ctx->acct, job_off + sizeof(Job));
+        st = resident_alloc(ctx, &ctx->acct, job_off + sizeof(Job));
         if (st != C2F_OK) return st;
     }
     Exec& ex = ctx->main;
@@ -2046,7 +2068,7 @@ c2f_status c2f_eval_ros(c2f_ctx* ctx, int32_t landscape_id, int32_t weather_id, 
     Exec& ex = ctx->main;
     const size_t n = (size_t)L.ncells();
     const size_t bytes = n * 8 * 7 + n * 64 + n * 32 + 9 * 256;   // 9 arrays, 256-byte aligned
-    c2f_status st = ensure_staging(ctx, ex, bytes);
+    c2f_status st = staging_room(ctx, ex, bytes);
     if (st != C2F_OK) return st;
     char* sb = (char*)ex.staging;
     EvalArgs a;
@@ -2165,7 +2187,7 @@ c2f_status c2f_autotune(c2f_ctx* ctx, const c2f_sim_params* rep) {
     Exec& ex = ctx->main;
     const int64_t n = L->ncells();
     uint32_t* counts = nullptr;
-    st = dev_alloc(ctx, (void**)&counts, (size_t)n * 4);
+    st = resident_alloc(ctx, (void**)&counts, (size_t)n * 4);
     if (st != C2F_OK) return st;
     c2f_outputs o;
     memset(&o, 0, sizeof o);
