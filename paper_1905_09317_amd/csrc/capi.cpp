@@ -2011,7 +2011,11 @@ c2f_status c2f_simulate_noalloc(c2f_ctx* ctx, const c2f_sim_params* params, cons
         ++ex.last.relaunches;
         if (cap >= cap_max)
             return fail(ctx, C2F_ECAPACITY, "work lists overflow at capacity %lld", (long long)cap);
-        cap = std::min(cap_max, cap * 4);
+        // four times as long, or, where that does not fit, as long as the scratch
+        // allows for one slot
+        const int64_t next = std::min(cap_max, cap * 4);
+        const int64_t room = avail > plane_b + 4 ? (int64_t)((avail - plane_b - 4) / kSlotListBytesPerEntry) : 0;
+        cap = room < next && room > cap ? room : next;
     }
 }
 
