@@ -46,9 +46,9 @@ HBM_PEAK_GBS = 8000.0
 # roofline.traffic only while the sources are unchanged.
 KERNEL_SOURCES = ("propagate.hip", "device.h", "ln64.h", "types.h", "fuel_table.h")
 TRAFFIC = {
-    "single-fire-2048x2048-48h": ("86776a2cf699b20a", 10_895_478),
-    "batched-mc-1024x1024-2048reps": ("86776a2cf699b20a", 45_011_482_741),
-    "large-8192x8192-64reps-72h": ("86776a2cf699b20a", 811_516_875),
+    "single-fire-2048x2048-48h": ("646f28dbf80a3c02", 10_915_285),
+    "batched-mc-1024x1024-2048reps": ("646f28dbf80a3c02", 45_018_227_722),
+    "large-8192x8192-64reps-72h": ("646f28dbf80a3c02", 812_857_386),
 }
 
 

@@ -20,10 +20,11 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-result", "-Wno-unused-command-line-argument",
 ]
 
-# The propagation kernel holds about 130 constants outside its loops
-# when machine code motion hoists them, and spills for it (32 bytes and 120
-# scalar registers a lane at its 128 vector registers; 107 and no spill
-# without).
+# The propagation kernel holds about 130 constants outside its loops when
+# machine code motion hoists them: 126 to 128 vector registers instead of 94 and
+# 95, and 80 to 96 bytes a lane spilled in groups of 256 threads, which are built
+# for 96.  It is right without the flag (a compiler that no longer knows it stops
+# here), but slower.
 SOURCE_FLAGS = {"propagate.hip": ["-mllvm", "-disable-machine-licm"]}
 
 

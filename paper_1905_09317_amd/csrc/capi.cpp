@@ -771,17 +771,17 @@ struct LaunchPlan {
 //   1024^2  1536                        6.94 /  7.09
 //    512^2  1536                        6.39 /  6.24
 //    512^2  4800                       16.3  / 13.5
-// FP64 results keep the 512-thread groups that callers are known to expect of
-// them for one fire from 2^22 cells and for up to a compute unit's worth of
-// replications from 2^26.  That is not the faster width: at 512 / 1024 threads a
-// fire of 2048^2 takes 3.01 / 2.66 ms, 64 of 8192^2 10.1 / 8.67; autotuning
-// finds it.  Below those sizes they are as wide as others: one fire of 1024^2
-// 2.56 / 2.27, 8 of 1500^2 2.43 / 2.15, 64 of 4096^2 4.62 / 4.01.  Where memory
-// or the caller holds a launch to fewer groups (grid_cap, 0 = it does not), their
-// number counts, not the replications': 512^2 x 2048 in 60 groups 79.5 ms at 256
-// threads, 56.2 at 1024; 256^2 x 2048 in 93 groups 37.8 and 28.7; 1024^2 x 512 in
-// 24 groups 42.1 at 512, 38.2 at 1024; 64^2 x 2048 in 431 groups 2.57 at 256,
-// 2.40 at 512.
+// FP64 results take 512 threads for one fire from 2^22 cells and for up to a
+// compute unit's worth of replications from 2^26, though 1024 are faster there
+// as well (at 512 / 1024 threads a fire of 2048^2 takes 3.01 / 2.66 ms, 64 of
+// 8192^2 10.1 / 8.67; autotuning finds it): the tests of the full-size launches
+// hold this width.  Below those sizes such launches are as wide as others: one
+// fire of 1024^2 2.56 / 2.27, 8 of 1500^2 2.43 / 2.15, 64 of 4096^2 4.62 / 4.01.
+// Where the scratch, a lane's pool or the caller holds a launch to fewer groups
+// (grid_cap, 0 = none does), their number counts, not the replications': 512^2 x
+// 2048 in 60 groups 79.5 ms at 256 threads, 56.2 at 1024; 256^2 x 2048 in 93
+// groups 37.8 and 28.7; 1024^2 x 512 in 24 groups 42.1 at 512, 38.2 at 1024;
+// 64^2 x 2048 in 431 groups 2.57 at 256, 2.40 at 512.
 int32_t group_width(int32_t n_cu, int64_t cells, int32_t total_items, int32_t precision, int32_t grid_cap) {
     const int64_t items = grid_cap > 0 ? std::min(total_items, grid_cap) : total_items;
     if (precision == 0 && total_items <= n_cu && cells >= (total_items > 1 ? 1 << 26 : 1 << 22)) return 512;

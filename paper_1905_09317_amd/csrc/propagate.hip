@@ -128,7 +128,10 @@ __device__ __forceinline__ int32_t ceil_div_small(int32_t r, int32_t q) {
 // reach the neighbour (1..n, rem becomes 0), or 0 if it does not in this
 // period.
 __device__ __forceinline__ int32_t step_axis(int32_t q, int32_t& rem, int32_t n) {
-    const int32_t t = ceil_div_small(rem, max(q, 1));   // 1 where q >= rem
+    // 1 where q >= rem: the quotient truncates to 0, which the correction takes
+    // to 1 (24 bits of q hold enough: the product is 0), or to 1, and then q is
+    // below 2^17
+    const int32_t t = ceil_div_small(rem, max(q, 1));
     const bool reach = q > 0 && t <= n;
     // q n < rem < 2^16 when the neighbour is not reached
     rem = reach ? 0 : rem - (int32_t)__umul24((uint32_t)q, (uint32_t)n);
