@@ -430,25 +430,24 @@ __device__ R surface_consumption(int f, R ffmc, R bui) {
     }
 }
 
-// Fill one table row from FFMC, BUI, wind speed (km/h) and the azimuth the
-// wind comes from, one wave together (lane f takes fuel f).  The fire heads
-// downwind: WAZ = WD + 180 degrees.
+// Fill a table row from FFMC, BUI, wind speed (km/h) and the azimuth the wind
+// comes from: fuels f0, f0 + step, ... of it, and with fuel 0 what the fuels
+// share.  The fire heads downwind: WAZ = WD + 180 degrees.
 template <typename R>
-__device__ void weather_row(const CoefR<R>* coef, float ffmc_f, float bui_f, float ws_f, float wd_f,
-                            R* row) {
-    const R ffmc = (R)ffmc_f, bui = (R)bui_f, ws = (R)ws_f, wd = (R)wd_f;
+__device__ __forceinline__ void weather_row(const CoefR<R>* coef, const float* w, int f0, int step, R* row) {
+    const R ffmc = (R)w[0], bui = (R)w[1], ws = (R)w[2], wd = (R)w[3];
     const R m = (R)147.2 * ((R)101 - ffmc) / ((R)59.5 + ffmc);   // fine fuel moisture
     const R ff = (R)91.9 * m_exp((R)-0.1386 * m) * ((R)1 + m_pow(m, (R)5.31) / (R)4.93e7);
     const R isz = (R)0.208 * ff;
-    const int f = (int)threadIdx.x;
-    if (f == 0) {
+    if (f0 == 0) {
         const R waz = m_fmod(wd + (R)180, (R)360) * (Const<R>::pi / (R)180);
         row[0] = ff;
         row[1] = isz;
         row[2] = ws * m_sin(waz);
         row[3] = ws * m_cos(waz);
     }
-    if (f < kNumFuels) {
+#pragma unroll
+    for (int f = f0; f < kNumFuels; f += step) {
         const CoefR<R>& k = coef[f];
         R be = (R)1;
         if (f != kNonFuel && bui > (R)0)
@@ -457,27 +456,51 @@ __device__ void weather_row(const CoefR<R>* coef, float ffmc_f, float bui_f, flo
         row[kRowG + f] = (k.a > (R)0) ? -m_expm1(-k.b * isz) : (R)0;
         row[kRowSFC + f] = surface_consumption<R>(f, ffmc, bui);
     }
-    if (f < kRowLen - kRowSFC - kNumFuels) row[kRowSFC + kNumFuels + f] = (R)0;
+#pragma unroll
+    for (int f = f0; f < kRowLen - kRowSFC - kNumFuels; f += step) row[kRowSFC + kNumFuels + f] = (R)0;
 }
 
-// One wave a row, lane f for fuel f; blockIdx.y selects the precision.  (One
-// thread a row took its 19 fuels in turn: 10.4 + 4.8 us for up to 100 rows in
-// two launches, 9 us here.)  A launch holds fewer than 2^32 threads along an
-// axis, and a table up to 2^26 rows, so a wave takes several from 2^20 on.
-constexpr int kWeatherWaves = 1 << 20;
-
-__global__ __launch_bounds__(64) void weather_table_kernel(const float* __restrict__ wx, int n_rows,
-                                                           double* __restrict__ t64, float* __restrict__ t32) {
-    for (size_t i = blockIdx.x; i < (size_t)n_rows; i += gridDim.x) {
-        const float* w = wx + i * 4;
-        if (blockIdx.y == 0) weather_row<double>(coef_table<double>(), w[0], w[1], w[2], w[3], t64 + i * kRowLen);
-        else weather_row<float>(coef_table<float>(), w[0], w[1], w[2], w[3], t32 + i * kRowLen);
-    }
+// A wave a row, lane f for fuel f; blockIdx.y selects the precision.
+__global__ __launch_bounds__(64) void weather_table_kernel(const float* __restrict__ wx, double* __restrict__ t64,
+                                                           float* __restrict__ t32) {
+    const size_t i = blockIdx.x;
+    if (blockIdx.y == 0) weather_row<double>(coef_table<double>(), wx + i * 4, (int)threadIdx.x, 64, t64 + i * kRowLen);
+    else weather_row<float>(coef_table<float>(), wx + i * 4, (int)threadIdx.x, 64, t32 + i * kRowLen);
 }
+
+// A lane a row: the fuels in turn, the same branch for all lanes, and the row
+// written in one piece.
+template <typename R>
+__device__ __forceinline__ void weather_lane(const float* w, R* __restrict__ out) {
+    R row[kRowLen];
+    weather_row<R>(coef_table<R>(), w, 0, 1, row);
+#pragma unroll
+    for (int k = 0; k < kRowLen; ++k) out[k] = row[k];
+}
+
+__global__ __launch_bounds__(64) void weather_table_long_kernel(const float* __restrict__ wx, int n_rows,
+                                                                double* __restrict__ t64, float* __restrict__ t32) {
+    const size_t i = (size_t)blockIdx.x * 64 + threadIdx.x;
+    if (i >= (size_t)n_rows) return;
+    if (blockIdx.y == 0) weather_lane<double>(wx + i * 4, t64 + i * kRowLen);
+    else weather_lane<float>(wx + i * 4, t32 + i * kRowLen);
+}
+
+// Up to this many rows a wave each (one or two a SIMD in two precisions), more a
+// lane each.  Bound by a row's chain of exponentials and powers, then, from about
+// 2^16 rows, by the writes (768 B a row).  us for a wave / a lane a row: 48 rows
+// 7.5 / 8.0, 1000 8.0 / 9.7, 2000 15.4 / 11.5, 16000 87 / 14.5, 65536 338 / 26;
+// 2^20 rows 299.  (A lane a row, one launch a precision: 12.7, 17, 20, 21, 34, 300.)
+// A wave each does not reach the largest table, 2^26 rows: a launch holds fewer
+// than 2^32 threads along an axis.
+constexpr int kWeatherWaves = 1024;
 
 hipError_t launch_weather_table(const float* wx, int n_rows, double* t64, float* t32, hipStream_t s) {
-    const unsigned waves = (unsigned)(n_rows < kWeatherWaves ? n_rows : kWeatherWaves);
-    hipLaunchKernelGGL(weather_table_kernel, dim3(waves, 2), dim3(64), 0, s, wx, n_rows, t64, t32);
+    if (n_rows <= kWeatherWaves)
+        hipLaunchKernelGGL(weather_table_kernel, dim3((unsigned)n_rows, 2), dim3(64), 0, s, wx, t64, t32);
+    else
+        hipLaunchKernelGGL(weather_table_long_kernel, dim3((unsigned)((n_rows + 63) / 64), 2), dim3(64), 0, s, wx,
+                           n_rows, t64, t32);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
-"""Weather tables of more rows than a launch has waves (one short of it, one
-beyond, and the largest table there is): the rates of rows at both ends and on
-either side of a wave's second row against the oracle's."""
+"""Weather tables on either side of the line between a wave and a lane a row,
+long ones whose last wave is not full, and the largest there is: the rates of
+rows at both ends and in between against the oracle's."""
 import numpy as np
 import pytest
 
@@ -10,7 +10,7 @@ from paper_1905_09317_amd import Simulator
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_rows", [(1 << 20) - 1, (1 << 20) + 1, 1 << 26])
+@pytest.mark.parametrize("n_rows", [1024, 1025, (1 << 20) - 1, (1 << 20) + 1, 1 << 26])
 def test_rates_of_long_weather_tables(n_rows):
     fuel = np.array([[2, 15, 6, 11, 18]], np.uint8)
     i = np.arange(n_rows, dtype=np.uint32)
@@ -23,7 +23,7 @@ def test_rates_of_long_weather_tables(n_rows):
     print(f"weather rows: {n_rows}", flush=True)
     with Simulator(0) as sim:
         land, w = sim.load_landscape(fuel), sim.set_weather(wx)
-        for k in sorted({0, 1, (1 << 20) - 2, min(1 << 20, n_rows - 1), n_rows // 2, n_rows - 1}):
+        for k in sorted({0, 1, 63, 64, n_rows // 2, n_rows - 2, n_rows - 1}):
             one = wx[k:k + 1]
             for precision in (0, 1):
                 g = sim.eval_ros(land, w, scenario=k, precision=precision)
