@@ -55,7 +55,7 @@ TRAFFIC = {
 # The same for the scar comparison kernel (one launch per comparison of the
 # 2048^2 x 48-period workload).
 SCAR_SOURCES = ("metrics.hip",)
-SCAR_TRAFFIC = ("62393682e4706689", 218_838_464)
+SCAR_TRAFFIC = ("7dd26244cab4852f", 218_629_547)
 
 
 def kernel_digest(sources=KERNEL_SOURCES) -> str:

@@ -90,11 +90,13 @@ __device__ void finish_block(const uint32_t* part, int base, int len, unsigned l
 // Bound by the reference read.  The rows of a grid of n cells start n bytes
 // apart, so unless n is a multiple of 16 a lane's 16 bytes straddle words:
 // ALIGNED = false reads them with unaligned 16-byte loads (the last lane, whose
-// cells may end the row, byte by byte).  Periods are split over blockIdx.y in
-// batches while blocks are fewer than the compute units hold.  1001 x 777
-// cells x 24 periods took 129 us with one block per 2048 cells and period,
-// byte loads and ballots; 15.6 us here; 2048^2 x 48 took 50.0 us with a DPP sum and LDS atomics for
-// each period, 44.4 us with eight periods summed together (4.9 TB/s).
+// cells may end the row, takes the row's last 16 bytes: byte by byte, 15 loads a
+// period, it held up its block, 333 x 777 cells x 500 periods 80 us a call, 64 now).
+// Periods are split over blockIdx.y in batches while blocks are fewer than the
+// compute units hold.  1001 x 777 cells x 24 periods took 129 us with one block
+// per 2048 cells and period, byte loads and ballots; 15.6 us here; 2048^2 x 48
+// took 50.0 us with a DPP sum and LDS atomics for each period, 44.4 us with eight
+// periods summed together (4.9 TB/s).
 constexpr int kRowsBlock = 1024;
 constexpr int kRowsPeriods = 1024;   // a block's periods at most, 20 bytes of LDS each
 // kRowsMaxBlocks blocks of 16384 cells a stride reach 2^31 - 2 cells in 64
@@ -141,6 +143,28 @@ __device__ __forceinline__ uint32_t top_bits(uint32_t a, uint32_t b, uint32_t c,
     return ((ab & 0xC0C0C0C0u) | (cd >> 2 & ~0xC0C0C0C0u)) & 0xF0F0F0F0u;
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The n < 16 bytes at p, zeros above them (a grid of fewer than 16 cells).
+__device__ __forceinline__ u32x4 few_bytes(const uint8_t* p, int n) {
+    uint64_t lo = 0, hi = 0;
+#pragma unroll 1
+    for (int u = 0; u < n; ++u) {
+        const uint64_t b = p[u];
+        if (u < 8) lo |= b << (8 * u);
+        else hi |= b << (8 * (u - 8));
+    }
+    return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+// Drops the lowest n of 16 bytes (0 < n < 16), zeros come in above.
+__device__ __forceinline__ void drop_bytes(uint32_t* w, int n) {
+    const uint64_t lo = (uint64_t)w[0] | (uint64_t)w[1] << 32, hi = (uint64_t)w[2] | (uint64_t)w[3] << 32;
+    const int b = 8 * n;
+    const uint64_t l = b < 64 ? lo >> b | hi << (64 - b) : hi >> (b - 64), h = b < 64 ? hi >> b : 0ull;
+    w[0] = (uint32_t)l, w[1] = (uint32_t)(l >> 32), w[2] = (uint32_t)h, w[3] = (uint32_t)(h >> 32);
+}
+
 // Adds a row's packed sum to a period's count in LDS.
 __device__ __forceinline__ void add_row(unsigned long long* cnt, uint32_t r) {
     atomicAdd(cnt, (unsigned long long)(r & 1023u) | (unsigned long long)((r >> 10) & 1023u) << 21 |
@@ -154,7 +178,6 @@ __global__ __launch_bounds__(kRowsBlock) void scar_counts_rows_kernel(const int3
                                                                       unsigned long long* __restrict__ counts,
                                                                       uint32_t* __restrict__ ticket,
                                                                       double* __restrict__ out) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef u32x4 u32x4_u1 __attribute__((aligned(1)));
     typedef int32_t i32x4_u4 __attribute__((ext_vector_type(4), aligned(4)));
     extern __shared__ unsigned long long s_rows[];   // [periods of the block], then 3 u32 counts of each
@@ -163,8 +186,10 @@ __global__ __launch_bounds__(kRowsBlock) void scar_counts_rows_kernel(const int3
     __syncthreads();
     const int64_t q = (n + 15) / 16;
     for (int64_t jb = (int64_t)blockIdx.x * kRowsBlock; jb < q; jb += (int64_t)gridDim.x * kRowsBlock) {
+        // a wave without cells leaves its compute unit to the others
+        if (jb + (int64_t)(threadIdx.x & ~63u) >= q) break;
         const int64_t j = jb + threadIdx.x;
-        const int live = j < q ? (int)min((int64_t)16, n - 16 * j) : 0;   // the lane's cells
+        const int live = j < q ? (int)min((int64_t)16, n - 16 * j) : 0;   // the lane's cells (ALIGNED: all or none)
         int32_t kc[16];   // burn period of each of the lane's cells (0x7FFFFFFF = never)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -177,15 +202,19 @@ __global__ __launch_bounds__(kRowsBlock) void scar_counts_rows_kernel(const int3
                     const i32x4_u4 x = *(const i32x4_u4*)(arrival + 16 * j + 4 * v);
                     m[0] = x.x, m[1] = x.y, m[2] = x.z, m[3] = x.w;
                 }
-            } else {
+            } else if (!ALIGNED && live > 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) m[u] = arrival[min(16 * j + 4 * v + u, n - 1)];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (4 * v + u < live) m[u] = arrival[16 * j + 4 * v + u];
+                    if (4 * v + u >= live) m[u] = -1;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 kc[4 * v + u] = m[u] < 0 ? 0x7FFFFFFF : (m[u] == 0 ? 0 : (m[u] - 1) / period_min);
         }
+        // the last lane's cells are read from the end of the row, and moved down
+        const int over = live > 0 ? 16 - live : 0;
         for (int tw = p0; tw < p1; tw += kRowsWindow) {
             uint32_t kb[4];
 #pragma unroll
@@ -206,16 +235,16 @@ __global__ __launch_bounds__(kRowsBlock) void scar_counts_rows_kernel(const int3
                 for (int k = 0; k < kRowsBatch; ++k) {
                     u32x4 x = {0u, 0u, 0u, 0u};
                     const uint8_t* row = reference + (size_t)(t0 + k) * (size_t)n + 16 * (size_t)j;
-                    if (live == 16 && t0 + k < tend) {
+                    if (live > 0 && t0 + k < tend) {
                         if constexpr (ALIGNED) x = *(const u32x4*)row;
-                        else x = *(const u32x4_u1*)row;
+                        else if (n >= 16) x = *(const u32x4_u1*)(row - over);
+                        else x = few_bytes(row, live);
                     }
                     wb[k][0] = x.x, wb[k][1] = x.y, wb[k][2] = x.z, wb[k][3] = x.w;
-                    if (live > 0 && live < 16 && t0 + k < tend) {
+                }
+                if (!ALIGNED && over != 0 && n >= 16) {
 #pragma unroll
-                        for (int u = 0; u < 15; ++u)
-                            if (u < live) wb[k][u >> 2] |= (uint32_t)row[u] << (8 * (u & 3));
-                    }
+                    for (int k = 0; k < kRowsBatch; ++k) drop_bytes(wb[k], over);
                 }
                 uint32_t r[kRowsBatch];
 #pragma unroll
